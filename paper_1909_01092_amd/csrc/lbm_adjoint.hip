@@ -100,7 +100,7 @@ __global__ __launch_bounds__(NB) void k_adj_record(RecArgs a) {
     const int z = (int)(n / ((int64_t)g.nx * g.ny));
     const PullCtx<S, T> pc = pull_ctx<S, T>(a.src, D, g);
     T d[2][Q];
-    pull_node(pc, pidx(x, y, z, g), d);
+    pull_node(pc, x, y, z, d);
     NodeM<T, true> m;
     node_moments(d, m);
     T *rec = static_cast<T *>(a.rec);

@@ -64,9 +64,9 @@ void init_org(const lbm_params &q, int32_t org[3]) {
 
 struct Layout {
     size_t tables, desc, state, pop[2], part1, part3, raw, vrho, rho_n, pmask, series, aux, total;
-    std::vector<int64_t> pop_off, bbox_off, part3_off, series_off, init_wg;
+    std::vector<int64_t> pop_off, ck_off, bbox_off, part3_off, series_off, init_wg;
     std::vector<int> S, k3_count;
-    int64_t Ntot = 0, NPtot = 0, S3tot = 0, part3_tot = 0, series_tot = 0, init_tot = 0;
+    int64_t Ntot = 0, pop_elems = 0, ck_elems = 0, ck_max = 0, S3tot = 0, part3_tot = 0, series_tot = 0, init_tot = 0;
     size_t aux_doubles = 0;
 };
 
@@ -77,7 +77,7 @@ Layout plan(const Groups &G, int prec) {
     const lbm_params *p = G.q.data();
     const int n = (int)G.q.size();
     const size_t es = elem_size(prec);
-    L.pop_off.resize(n); L.bbox_off.resize(n); L.part3_off.resize(n);
+    L.pop_off.resize(n); L.ck_off.resize(n); L.bbox_off.resize(n); L.part3_off.resize(n);
     L.series_off.resize(n); L.S.resize(n); L.k3_count.resize(n); L.init_wg.resize(n);
     size_t max_cols = 0;
     for (int r = 0; r < n; r++) {
@@ -85,11 +85,16 @@ Layout plan(const Groups &G, int prec) {
         const int64_t N = (int64_t)p[r].nx * p[r].ny * p[r].nz;
         const int64_t NP = (int64_t)(p[r].nx + 2) * (p[r].ny + 2) * (p[r].nz + 2);
         if (primary) {
-            L.pop_off[r] = 38 * L.NPtot;
-            L.NPtot += NP;
+            // replica blocks start on cache lines
+            L.pop_off[r] = (L.pop_elems + 63) / 64 * 64;
+            L.pop_elems = L.pop_off[r] + 38 * (int64_t)p[r].nx * (p[r].ny + 2) * (p[r].nz + 2);
+            L.ck_off[r] = L.ck_elems;
+            L.ck_elems += 38 * NP;
+            L.ck_max = std::max(L.ck_max, NP);
             L.Ntot += N;
         } else {
             L.pop_off[r] = L.pop_off[G.prim[r]];
+            L.ck_off[r] = L.ck_off[G.prim[r]];
         }
         L.S[r] = bbox_edge(p[r]);
         const int64_t S3 = (int64_t)L.S[r] * L.S[r] * L.S[r];
@@ -110,8 +115,8 @@ Layout plan(const Groups &G, int prec) {
     L.tables = take(sizeof(int32_t) * 3 * (n + 1));
     L.desc = take(sizeof(RepDesc) * n);
     L.state = take(sizeof(RepState) * n);
-    L.pop[0] = take(38 * L.NPtot * es);
-    L.pop[1] = take(38 * L.NPtot * es);
+    L.pop[0] = take(L.pop_elems * es);
+    L.pop[1] = take(L.pop_elems * es);
     L.part1 = take(sizeof(double) * std::max<int64_t>(L.part3_tot, 1));
     L.part3 = take(sizeof(double) * std::max<int64_t>(L.part3_tot, 1));
     L.raw = take(sizeof(double) * std::max<int64_t>(RAW * L.S3tot, 1));
@@ -615,7 +620,8 @@ LBM_API int lbm_init(const lbm_params *p_in, int32_t n_replicas, int32_t precisi
         std::memset(&D, 0, sizeof(D));
         D.nx = q.nx; D.ny = q.ny; D.nz = q.nz; D.walls = q.walls;
         D.N = (int64_t)q.nx * q.ny * q.nz;
-        D.NP = (int64_t)(q.nx + 2) * (q.ny + 2) * (q.nz + 2);
+        D.ck_NP = (int64_t)(q.nx + 2) * (q.ny + 2) * (q.nz + 2);
+        D.ck_off = L.ck_off[r];
         D.pop_off = L.pop_off[r];
         D.S = L.S[r];
         D.has_particle = has_sphere(q);
@@ -639,11 +645,6 @@ LBM_API int lbm_init(const lbm_params *p_in, int32_t n_replicas, int32_t precisi
         if (q.kT > 0.0) c->noise = 1;
         D.init_amp = q.init_amp;
         D.init_split = q.init_split;
-        // rows of at most two cache lines (padded): their x-ghost elements sit in
-        // lines shared with row ends, so filling them saves a read-modify-write
-        // per line (32x32x128 replicas: 2055 -> 1677 us per main kernel; rows
-        // of 264 bytes and more are faster without)
-        D.ghost_fill = (int32_t)((size_t)(q.nx + 2) * elem_size(precision) <= 256);
         D.key0 = (uint32_t)(q.seed & 0xffffffffu);
         D.key1 = (uint32_t)(q.seed >> 32) ^ (uint32_t)q.replica;
         D.noise_diffusive = q.noise_diffusive;
@@ -864,7 +865,7 @@ LBM_API int lbm_populations(lbm_ctx *c, int32_t replica, double *host_f) {
     if (!host_f) return fail(c, LBM_EINVAL, "host_f is NULL");
     const lbm_params &q = c->p[replica];
     const int64_t plane = (int64_t)q.nx * q.ny, N = plane * q.nz;
-    const size_t cap = 38 * c->L.NPtot * c->es;  // the free population buffer is the scratch
+    const size_t cap = c->L.pop_elems * c->es;  // the free population buffer is the scratch
     int zs = (int)std::max<int64_t>(1, std::min<int64_t>(q.nz, cap / (38 * plane * sizeof(double))));
     std::vector<double> host((size_t)38 * plane * zs);
     for (int z0 = 0; z0 < q.nz; z0 += zs) {
@@ -984,16 +985,34 @@ LBM_API int lbm_u_series(lbm_ctx *c, int32_t replica, double *host_u3, int64_t c
 
 LBM_API int lbm_checkpoint_bytes(lbm_ctx *c, size_t *bytes) {
     if (!c || !bytes) return LBM_EINVAL;
-    *bytes = 38 * c->L.NPtot * c->es + sizeof(RepState) * c->nrep +
+    *bytes = c->L.ck_elems * c->es + sizeof(RepState) * c->nrep +
              (sizeof(double) * 2 + sizeof(uint32_t)) * c->L.S3tot;
     return LBM_OK;
 }
 
+namespace {
+// the current populations into (save) or out of a checkpoint's population part
+int copy_populations(lbm_ctx *c, bool save, char *ck) {
+    CkArgs a;
+    a.desc = c->d_desc();
+    a.pop = c->d_pop(c->cur);
+    a.ck = ck;
+    const int blocks = (int)((c->L.ck_max + 255) / 256);
+    for (int r = 0; r < c->nrep; r += 32768) {  // the grid's y extent holds 65535
+        a.rep0 = r;
+        const hipError_t e = launch_ck(c->prec, save, a, blocks, std::min(c->nrep - r, 32768), c->stream);
+        if (e != hipSuccess) return hip_fail(c, e, "checkpoint kernel launch");
+    }
+    return LBM_OK;
+}
+}  // namespace
+
 LBM_API int lbm_checkpoint(lbm_ctx *c, void *dev_dst) {
     if (!c || !dev_dst) return LBM_EINVAL;
     char *d = reinterpret_cast<char *>(dev_dst);
-    const size_t pb = 38 * c->L.NPtot * c->es, sb = sizeof(RepState) * c->nrep;
-    HIP_TRY(c, hipMemcpyAsync(d, c->d_pop(c->cur), pb, hipMemcpyDeviceToDevice, c->stream));
+    const size_t pb = c->L.ck_elems * c->es, sb = sizeof(RepState) * c->nrep;
+    int rc = copy_populations(c, true, d);
+    if (rc != LBM_OK) return rc;
     HIP_TRY(c, hipMemcpyAsync(d + pb, c->d_state(), sb, hipMemcpyDeviceToDevice, c->stream));
     if (c->L.S3tot) {
         HIP_TRY(c, hipMemcpyAsync(d + pb + sb, c->d_vrho(), sizeof(double) * 2 * c->L.S3tot,
@@ -1009,8 +1028,9 @@ LBM_API int lbm_restore(lbm_ctx *c, const void *dev_src) {
     if (!c || !dev_src) return LBM_EINVAL;
     c->tape.valid = false;
     const char *d = reinterpret_cast<const char *>(dev_src);
-    const size_t pb = 38 * c->L.NPtot * c->es, sb = sizeof(RepState) * c->nrep;
-    HIP_TRY(c, hipMemcpyAsync(c->d_pop(c->cur), d, pb, hipMemcpyDeviceToDevice, c->stream));
+    const size_t pb = c->L.ck_elems * c->es, sb = sizeof(RepState) * c->nrep;
+    int rc = copy_populations(c, false, const_cast<char *>(d));
+    if (rc != LBM_OK) return rc;
     HIP_TRY(c, hipMemcpyAsync(c->d_state(), d + pb, sb, hipMemcpyDeviceToDevice, c->stream));
     if (c->L.S3tot) {
         HIP_TRY(c, hipMemcpyAsync(c->d_vrho(), d + pb + sb, sizeof(double) * 2 * c->L.S3tot,

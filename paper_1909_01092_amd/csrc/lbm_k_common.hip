@@ -157,6 +157,12 @@ hipError_t launch_export(int prec, const ExportArgs &a, int64_t count, hipStream
     return launch_export_f16(a, count, s);
 }
 
+hipError_t launch_ck(int prec, bool save, const CkArgs &a, int blocks, int nrep, hipStream_t s) {
+    if (prec == 0) return launch_ck_f64(save, a, blocks, nrep, s);
+    if (prec == 1) return launch_ck_f32(save, a, blocks, nrep, s);
+    return launch_ck_f16(save, a, blocks, nrep, s);
+}
+
 hipError_t launch_fields(int prec, const FieldArgs &a, int64_t N, int64_t plane, hipStream_t s) {
     hipError_t e = prec == 0 ? launch_fields_a_f64(a, N, s)
                  : prec == 1 ? launch_fields_a_f32(a, N, s) : launch_fields_a_f16(a, N, s);

@@ -76,6 +76,13 @@ struct ExportArgs {
     double *out;
 };
 
+struct CkArgs {
+    const RepDesc *desc;
+    int32_t rep0;              // first entry of the launch (grid y)
+    void *pop;                 // population buffer
+    void *ck;                  // population part of a checkpoint
+};
+
 struct FieldArgs {
     const RepDesc *desc;
     const RepState *state;
@@ -93,6 +100,7 @@ hipError_t launch_links(int prec, const LinkArgs &a, int grid, hipStream_t s);
 hipError_t launch_particle(int prec, const ParticleArgs &a, int grid, hipStream_t s);
 hipError_t launch_init(int prec, const InitArgs &a, int grid, int nrep, hipStream_t s);
 hipError_t launch_export(int prec, const ExportArgs &a, int64_t count, hipStream_t s);
+hipError_t launch_ck(int prec, bool save, const CkArgs &a, int blocks, int nrep, hipStream_t s);
 hipError_t launch_fields(int prec, const FieldArgs &a, int64_t N, int64_t plane, hipStream_t s);
 
 #define LBM_DECLARE(SUFFIX)                                                                        \
@@ -101,6 +109,7 @@ hipError_t launch_fields(int prec, const FieldArgs &a, int64_t N, int64_t plane,
     hipError_t launch_particle_##SUFFIX(const ParticleArgs &, int, hipStream_t);                   \
     hipError_t launch_init_##SUFFIX(const InitArgs &, int, hipStream_t);                           \
     hipError_t launch_export_##SUFFIX(const ExportArgs &, int64_t, hipStream_t);                   \
+    hipError_t launch_ck_##SUFFIX(bool, const CkArgs &, int, int, hipStream_t);                    \
     hipError_t launch_fields_a_##SUFFIX(const FieldArgs &, int64_t, hipStream_t);
 LBM_DECLARE(f64)
 LBM_DECLARE(f32)

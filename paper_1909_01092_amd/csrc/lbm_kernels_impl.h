@@ -9,16 +9,27 @@
 // leap-frog Newton, moving bounce-back with momentum exchange,
 // cover/uncover, mass correction, virtual wetting layer).  Sec. 3: eq. (fp).
 //
-// Storage.  Each replica keeps its populations on a lattice padded by one
-// ghost layer per side, [component][direction][z+1][y+1][x+1].  Node x pulls
-// population i of step n from the padded position x - c_i, slot i.  Whoever
-// produces a value that does not arrive by plain streaming writes it into
-// exactly that slot: a node next to a wall writes its bounced value into the
-// wall's ghost, a node next to a periodic face writes the wrapped copy into
-// the ghost, the link kernel writes the sphere's moving-wall bounce-back into
-// the particle node's slot, and uncovered nodes get f_eq written into the
-// slots they pull from.  Every pull is therefore 38 loads at wave-uniform
-// offsets from the node's own index.
+// Storage.  Each replica keeps its populations on a lattice with one ghost row
+// per y side and one ghost plane per z side, laid out
+// [z+1][y+1][component][direction][x]: the 38 slots of an x-row lie next to
+// each other, rows follow without padding.  Node x pulls population i of step
+// n from position x - c_i, slot i, x wrapped around the row; a node whose
+// x - c_i lies beyond an x-wall pulls slot opp(i) of itself (half-way
+// bounce-back).  Whoever produces a value that does not arrive that way writes
+// it into exactly the slot it is pulled from: a node next to a y- or z-wall
+// writes its bounced value into the ghost, a node next to a periodic y- or
+// z-face writes the wrapped copy into the ghost, the link kernel writes the
+// sphere's moving-wall bounce-back into the particle node's slot, and uncovered
+// nodes get f_eq written into the slots they pull from.
+// Why this order: a wave reads and writes 76 streams.  With one array per
+// direction these are 76 distant pages and, with ghost columns, rows that
+// start inside a cache line which two rows share.  Slots side by side make
+// every line of a tile's rows whole and put the streams of a row into a few
+// pages: 38 loads and 38 stores per node without the collision move 5.2
+// against 2.9 TB/s on rows of 32 FP32 nodes, 5.2 against 3.6 on 64, 4.6
+// against 3.4 on 60, 5.1 against 4.0 on 192 FP16 nodes.  Padding the rows to
+// whole lines loses where nx is no multiple of a line (3.3 TB/s at 60 nodes)
+// and changes nothing where it is.
 //
 // One step = k_main (all nodes of all replicas) + k_links + k_particle
 // (bounding box of each sphere).
@@ -57,8 +68,6 @@ struct Geo {
     int nx, ny, nz;
     bool wx, wy, wz;
     int64_t N;          // nodes
-    int PX, PY;         // padded row and plane widths (nx + 2, ny + 2)
-    uint32_t NP;        // padded nodes per component and direction
 };
 
 __device__ __forceinline__ Geo geo_of(const RepDesc &D) {
@@ -66,15 +75,25 @@ __device__ __forceinline__ Geo geo_of(const RepDesc &D) {
     g.nx = D.nx; g.ny = D.ny; g.nz = D.nz;
     g.wx = D.walls & 1u; g.wy = D.walls & 2u; g.wz = D.walls & 4u;
     g.N = D.N;
-    g.PX = D.nx + 2;
-    g.PY = D.ny + 2;
-    g.NP = (uint32_t)D.NP;
     return g;
 }
 
-// padded index of lattice position (x, y, z), -1 <= x <= nx etc.
-__device__ __forceinline__ uint32_t pidx(int x, int y, int z, const Geo &g) {
-    return (uint32_t)(x + 1) + (uint32_t)g.PX * ((uint32_t)(y + 1) + (uint32_t)g.PY * (uint32_t)(z + 1));
+// element strides of a replica block: a row's 38 slots, a plane with its two
+// ghost rows (fits 31 bits in bytes for every accepted lattice)
+__device__ __forceinline__ int row_stride(const Geo &g) { return 2 * Q * g.nx; }
+__device__ __forceinline__ int plane_stride(const Geo &g) { return 2 * Q * g.nx * (g.ny + 2); }
+
+// element of slot s (19 l + i) at position (x, y, z), 0 <= x < nx, -1 <= y <= ny, -1 <= z <= nz
+__device__ __forceinline__ int64_t slot_at(int x, int y, int z, int s, const Geo &g) {
+    return (int64_t)(z + 1) * plane_stride(g) + (int64_t)(y + 1) * row_stride(g) + s * g.nx + x;
+}
+
+// element that node (x, y, z) pulls population i of component l from
+__device__ __forceinline__ int64_t pull_slot(int x, int y, int z, int l, int i, const Geo &g) {
+    const int sx = x - cx(i);
+    if (sx >= 0 && sx < g.nx) return slot_at(sx, y - cy(i), z - cz(i), l * Q + i, g);
+    if (g.wx) return slot_at(x, y, z, l * Q + opp(i), g);
+    return slot_at(sx < 0 ? sx + g.nx : sx - g.nx, y - cy(i), z - cz(i), l * Q + i, g);
 }
 // unpadded node index (noise counter, fields)
 __device__ __forceinline__ uint32_t nidx(int x, int y, int z, const Geo &g) {
@@ -88,11 +107,6 @@ __device__ __forceinline__ bool wrap1(int &v, int n, bool wall) {
     }
     return true;
 }
-// padded-index offset of direction i
-__device__ __forceinline__ int32_t doff(int i, const Geo &g) {
-    return cx(i) + g.PX * (cy(i) + g.PY * cz(i));
-}
-
 // wall layers mirror onto the adjacent node, periodic axes wrap
 __device__ __forceinline__ int mirror1(int v, int n, bool wall) {
     if (v < 0) return wall ? 0 : v + n;
@@ -164,12 +178,13 @@ __device__ __forceinline__ bool bbox_pos(int b, const int32_t *org, int S, const
 }
 
 // ------------------------------------------------------------------ pulling
-// Populations f_{l i}(x, n) of a fluid node in deviation form: slot i at the
-// padded position x - c_i (see the storage note at the top).
+// Populations f_{l i}(x, n) of a fluid node in deviation form (see the storage
+// note at the top for where each comes from).
 template <typename S, typename T>
 struct PullCtx {
     const S *src;          // replica block
-    int32_t NP, PX, PXY;   // padded sizes
+    int32_t nx, RS, PS;    // row length, row and plane strides
+    bool wx;
     T scale[2];            // FP16 relative storage: rho0_l (times w_i per slot)
 };
 
@@ -177,34 +192,89 @@ template <typename S, typename T>
 __device__ __forceinline__ PullCtx<S, T> pull_ctx(const void *buf, const RepDesc &D, const Geo &g) {
     PullCtx<S, T> pc;
     pc.src = reinterpret_cast<const S *>(buf) + D.pop_off;
-    pc.NP = (int32_t)g.NP;
-    pc.PX = g.PX;
-    pc.PXY = g.PX * g.PY;
+    pc.nx = g.nx;
+    pc.RS = row_stride(g);
+    pc.PS = plane_stride(g);
+    pc.wx = g.wx;
     for (int l = 0; l < 2; l++) pc.scale[l] = Rel<S>::value ? T(D.rho0[l]) : T(1);
     return pc;
 }
 
-// element at a wave-uniform base plus a per-lane byte offset (lets the
-// compiler use scalar-base + 32-bit vector-offset addressing)
-template <typename S>
-__device__ __forceinline__ const S &at(const S *base, uint32_t byte_off) {
-    return *reinterpret_cast<const S *>(reinterpret_cast<const char *>(base) + byte_off);
-}
-template <typename S>
-__device__ __forceinline__ S &at(S *base, uint32_t byte_off) {
-    return *reinterpret_cast<S *>(reinterpret_cast<char *>(base) + byte_off);
+// Buffer access: scalar base (64-bit, in a descriptor) + per-lane 32-bit byte
+// offset + scalar byte offset, so the 38 slots of a node cost one scalar
+// addition each and no vector address arithmetic.  Offsets stay below 4 GiB
+// (two planes of any accepted lattice do), so the descriptor's size check is
+// left open.
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+__device__ __forceinline__ Rsrc rsrc_of(const void *base) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, 0x00027000);
 }
 
+template <typename S>
+__device__ __forceinline__ S buf_ld(Rsrc r, uint32_t vo, uint32_t so) {
+    if constexpr (sizeof(S) == 8) return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0));
+    else if constexpr (sizeof(S) == 4) return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
+    else return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b16(r, vo, so, 0));
+}
+typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
+template <typename S>
+__device__ __forceinline__ void buf_st(S v, Rsrc r, uint32_t vo, uint32_t so) {
+    if constexpr (sizeof(S) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, v), r, vo, so, 0);
+    else if constexpr (sizeof(S) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, vo, so, 0);
+    else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, vo, so, 0);
+}
+
+// a wave-uniform value recomputed from here on instead of being kept (the
+// scalar registers do not hold every derived offset at once)
+__device__ __forceinline__ void renew(int32_t &v) { asm volatile("" : "+s"(v)); }
+
+// z uniform over the wave; (x, y) per lane
 template <typename S, typename T>
-__device__ __forceinline__ void pull_node(const PullCtx<S, T> &c, uint32_t own, T (&d)[2][Q]) {
-    const S *b0 = c.src, *b1 = c.src + Q * c.NP;
+__device__ __forceinline__ void pull_row(PullCtx<S, T> c, int x, int y, int z, T (&d)[2][Q]) {
+    constexpr uint32_t es = sizeof(S);
+    renew(c.nx);
+    renew(c.RS);
+    renew(c.PS);
+    const uint32_t nxb = (uint32_t)c.nx * es, RSb = (uint32_t)c.RS * es, PSb = (uint32_t)c.PS * es;
+    // bases two rows before plane z (c_z <= 0: plane z + 1 is one plane further)
+    // and before plane z - 1 (c_z > 0), so that no offset is negative
+    const S *pl = c.src + (int64_t)(z + 1) * c.PS - 2 * (int64_t)c.RS;
+    const Rsrc r0 = rsrc_of(pl), r1 = rsrc_of(pl - c.PS);
+    const bool lo = x == 0, hi = x == c.nx - 1;
+    const uint32_t own = (uint32_t)(y + 2) * RSb + (uint32_t)x * es;
+    const uint32_t vm = lo ? own + (nxb - es) : own - es, vp = hi ? own - (nxb - es) : own + es;
+    const bool wm = c.wx && lo, wp = c.wx && hi;
 #pragma unroll
     for (int i = 0; i < Q; i++) {
         const T w = T(wgt(i));
-        const int32_t off = cx(i) + c.PX * cy(i) + c.PXY * cz(i);
-        const uint32_t vo = (own + (uint32_t)(i * c.NP - off)) * (uint32_t)sizeof(S);
-        d[0][i] = ld_dev<S, T>(&at(b0, vo), w * c.scale[0]);
-        d[1][i] = ld_dev<S, T>(&at(b1, vo), w * c.scale[1]);
+        uint32_t vo = (cx(i) > 0 ? vm : cx(i) < 0 ? vp : own) + (cz(i) < 0 ? PSb : 0u);
+        if (cx(i)) {
+            // across an x-wall: the node's own slot opp(i), in plane z
+            const uint32_t k = (opp(i) > i ? nxb : 0u - nxb) + (cy(i) > 0 ? RSb : cy(i) < 0 ? 0u - RSb : 0u) +
+                               (cz(i) > 0 ? PSb : 0u);
+            vo = (cx(i) > 0 ? wm : wp) ? own + k : vo;
+        }
+        const uint32_t so = (uint32_t)(1 - cy(i)) * RSb + (uint32_t)i * nxb;
+        const Rsrc r = cz(i) > 0 ? r1 : r0;
+        const S a = buf_ld<S>(r, vo, so), b = buf_ld<S>(r, vo, so + (uint32_t)Q * nxb);
+        d[0][i] = ld_dev<S, T>(&a, w * c.scale[0]);
+        d[1][i] = ld_dev<S, T>(&b, w * c.scale[1]);
+    }
+}
+
+// any node
+template <typename S, typename T>
+__device__ __forceinline__ void pull_node(const PullCtx<S, T> &c, int x, int y, int z, T (&d)[2][Q]) {
+    const S *own = c.src + (int64_t)(z + 1) * c.PS + (int64_t)(y + 1) * c.RS + x;
+    const bool lo = x == 0, hi = x == c.nx - 1;
+    const int32_t dm = lo ? c.nx - 1 : -1, dp = hi ? 1 - c.nx : 1;
+#pragma unroll
+    for (int i = 0; i < Q; i++) {
+        const T w = T(wgt(i));
+        int32_t off = i * c.nx - cy(i) * c.RS - cz(i) * c.PS + (cx(i) > 0 ? dm : cx(i) < 0 ? dp : 0);
+        if (cx(i)) off = c.wx && (cx(i) > 0 ? lo : hi) ? opp(i) * c.nx : off;
+        d[0][i] = ld_dev<S, T>(own + off, w * c.scale[0]);
+        d[1][i] = ld_dev<S, T>(own + off + Q * c.nx, w * c.scale[1]);
     }
 }
 
@@ -357,7 +427,6 @@ void k_main(MainArgs a) {
 
     const bool hp = D.has_particle;
     const int nsph = GROUP ? D.n_sph : 1;
-    const bool ghost_fill = D.ghost_fill;
     const PullCtx<S, T> pc = pull_ctx<S, T>(a.src, D, g);
     const T dl[2] = {T(stp->delta[0]), T(stp->delta[1])};
     const double dld[2] = {stp->delta[0], stp->delta[1]};
@@ -368,7 +437,6 @@ void k_main(MainArgs a) {
     const double *__restrict__ vrho = a.vrho + D.bbox_off * 2;
     double *__restrict__ rho_n = a.rho_n + D.bbox_off * 2;
     S *__restrict__ dst = reinterpret_cast<S *>(a.dst) + D.pop_off;
-    const uint32_t NP = g.NP;
     const double rho0d[2] = {D.rho0[0], D.rho0[1]};
     const T G = sizeof(T) == 4 ? T(D.G32) : T(D.G);
     const T af[3] = {sizeof(T) == 4 ? T(D.af32[0]) : T(D.af[0]), sizeof(T) == 4 ? T(D.af32[1]) : T(D.af[1]),
@@ -411,7 +479,7 @@ void k_main(MainArgs a) {
             }
             if (vi < 0) {
                 T d[2][Q];
-                pull_node(pcl, pidx(xx, yy, zz, g), d);
+                pull_row(pcl, xx, yy, zz, d);
                 node_moments(d, s);
                 s.rd[0] += dl[0];
                 s.rd[1] += dl[1];
@@ -468,7 +536,7 @@ void k_main(MainArgs a) {
     for (int k = 0; k < nplanes; k++) {
         // keep uniform values derived from these roots inside the loop (scalar
         // recomputation is cheaper than spilling hoisted copies)
-        asm volatile("" : "+s"(k0), "+s"(k1), "+s"(pcl.NP), "+s"(pcl.PX), "+s"(pcl.PXY));
+        asm volatile("" : "+s"(k0), "+s"(k1), "+s"(pcl.nx), "+s"(pcl.RS), "+s"(pcl.PS));
         // face tests are redone per plane from these bits instead of being
         // hoisted as lane masks that would crowd the scalar registers
         asm volatile("" : "+v"(xyface));
@@ -480,7 +548,6 @@ void k_main(MainArgs a) {
         if (k < 2) continue;
         const int z = zp - dir;
         if (inner && cur_fluid) {
-            const uint32_t own = pidx(x, y, z, g);
             const T(&rd)[2] = cur.rd;
             const T(&j)[2][3] = cur.j;
             // Shan-Chen: F_l = -G rho_l sum_i w_i rho~_l'(x + c_i) c_i + rho_l a_f
@@ -531,7 +598,9 @@ void k_main(MainArgs a) {
             common_velocity(rd, j, F, zz, cf, u, xid);
             const bool zlo = z == 0, zhi = z == g.nz - 1;
             const bool yzface = (xyface & 12u) != 0u || zlo || zhi;
-            const bool xonly = !yzface && (xyface & 3u) != 0u;
+            S *dplane = dst + (int64_t)(z + 1) * pcl.PS;
+            const Rsrc drs = rsrc_of(dplane);
+            const uint32_t own = ((uint32_t)(y + 1) * (uint32_t)pcl.RS + (uint32_t)x) * (uint32_t)sizeof(S);
             constexpr int kCompUnroll = main_unroll<S, T, TAU1> ? 2 : 1;
 #pragma unroll kCompUnroll
             for (int l = 0; l < 2; l++) {
@@ -560,71 +629,39 @@ void k_main(MainArgs a) {
                     relax_component(r0l, sig, rdl, jl, ml, Fl, u, xid, zl, cf, out);
                 }
                 const T sc = Rel<S>::value ? r0l : T(1);
-                S *dl_base = dst + l * Q * pcl.NP;
-                const uint32_t own4 = own * (uint32_t)sizeof(S);
+                int32_t nxs = nx;
+                renew(nxs);
+                const uint32_t nxb = (uint32_t)nxs * (uint32_t)sizeof(S);
 #pragma unroll
                 for (int i = 0; i < Q; i++) {
                     const T inv = Rel<S>::value ? T(1) / (T(wgt(i)) * sc) : T(1);
-                    S *col = dl_base + i * pcl.NP;
-                    st_dev<S, T>(&at(col, own4), out[i], inv);
+                    S v;
+                    st_dev<S, T>(&v, out[i], inv);
+                    buf_st<S>(v, drs, own, (uint32_t)(l * Q + i) * nxb);
                 }
-                // Narrow rows: the two x-ghost elements between consecutive rows
-                // share a cache line with both rows' ends, and a line left partly
-                // unwritten costs a read-modify-write in HBM.  The x-face nodes
-                // then also fill the ghost slots no node ever pulls from (c_x <= 0
-                // beside x = 0, c_x >= 0 beside x = nx - 1), so every such line is
-                // written whole.
-                if (ghost_fill && (xyface & 3u) != 0u) {
-                    const bool hi = xyface & 2u;
-#pragma unroll
-                    for (int i = 0; i < Q; i++) {
-                        const T inv = Rel<S>::value ? T(1) / (T(wgt(i)) * sc) : T(1);
-                        if (hi ? cx(i) >= 0 : cx(i) <= 0) {
-                            const uint32_t e = (uint32_t)((int32_t)own + (hi ? 1 : -1) + i * pcl.NP);
-                            st_dev<S, T>(&at(dl_base, e * (uint32_t)sizeof(S)), out[i], inv);
-                        }
-                    }
-                }
-                // A link that leaves the box also writes its value where the
-                // receiver pulls it from: the wall ghost x + c_i, slot opp(i)
-                // (half-way bounce-back), or the periodic image of x, slot i.
-                // Only nodes on a face do.  Nodes on an x-face alone (the
-                // common case: two per row) write the links with c_x pointing
-                // out, at offsets uniform over the wave; nodes on a y- or
-                // z-face take the general form.
-                if (xonly) {
-                    const bool hi = xyface & 2u;
-#pragma unroll
-                    for (int i = 1; i < Q; i++) {
-                        if (cx(i) == 0) continue;
-                        const T inv = Rel<S>::value ? T(1) / (T(wgt(i)) * sc) : T(1);
-                        const int32_t so = g.wx ? opp(i) * pcl.NP + pcl.PX * cy(i) + pcl.PXY * cz(i) + cx(i)
-                                                : i * pcl.NP - cx(i) * nx;
-                        if ((cx(i) > 0) == hi) {
-                            const uint32_t e = (uint32_t)((int32_t)own + so);
-                            st_dev<S, T>(&at(dl_base, e * (uint32_t)sizeof(S)), out[i], inv);
-                        }
-                    }
-                }
+                // A link that leaves the box through a y- or z-face also writes its
+                // value where the receiver pulls it from: the wall ghost x + c_i,
+                // slot opp(i) (half-way bounce-back), or the periodic image of x,
+                // slot i.  (Through an x-face alone it is pulled from the node's
+                // own slot, and across an x-wall whatever the other axes are.)
                 if (yzface) {
                     const bool xlo = xyface & 1u, xhi = xyface & 2u, ylo = xyface & 4u, yhi = xyface & 8u;
 #pragma unroll
                     for (int i = 1; i < Q; i++) {
+                        if (cy(i) == 0 && cz(i) == 0) continue;
                         const T inv = Rel<S>::value ? T(1) / (T(wgt(i)) * sc) : T(1);
                         const bool ex = cx(i) > 0 ? xhi : (cx(i) < 0 ? xlo : false);
                         const bool ey = cy(i) > 0 ? yhi : (cy(i) < 0 ? ylo : false);
                         const bool ez = cz(i) > 0 ? zhi : (cz(i) < 0 ? zlo : false);
-                        if (ex || ey || ez) {
-                            // element index from the component base: slot * NP + target,
-                            // never negative (x + c_i lies in the ghost layer, the
-                            // periodic image x - n c_i inside the box)
-                            const bool bounce = (ex && g.wx) || (ey && g.wy) || (ez && g.wz);
-                            const int32_t so = bounce ? opp(i) * pcl.NP + pcl.PX * cy(i) + pcl.PXY * cz(i) + cx(i)
-                                                      : i * pcl.NP + (ex ? -cx(i) * nx : 0) +
-                                                            (ey ? -cy(i) * g.ny * g.PX : 0) +
-                                                            (ez ? -cz(i) * g.nz * g.PX * g.PY : 0);
-                            const uint32_t e = (uint32_t)((int32_t)own + so);
-                            st_dev<S, T>(&at(dl_base, e * (uint32_t)sizeof(S)), out[i], inv);
+                        if ((ey || ez) && !(ex && g.wx)) {
+                            const bool bounce = (ey && g.wy) || (ez && g.wz);
+                            const int32_t dx = ex ? cx(i) * (1 - nx) : cx(i);
+                            const int64_t so =
+                                bounce ? (int64_t)(opp(i) * pcl.nx + cy(i) * pcl.RS + dx) + (int64_t)cz(i) * pcl.PS
+                                       : (int64_t)(i * pcl.nx) - (int64_t)(ey ? cy(i) * g.ny : 0) * pcl.RS -
+                                             (int64_t)(ez ? cz(i) * g.nz : 0) * pcl.PS;
+                            S *base = dplane + l * Q * pcl.nx;
+                            st_dev<S, T>(reinterpret_cast<S *>(reinterpret_cast<char *>(base + so) + own), out[i], inv);
                         }
                     }
                 }
@@ -830,7 +867,6 @@ __global__ __launch_bounds__(B) void k_links(LinkArgs a) {
     double *raw = a.raw + D.bbox_off * RAW;
     S *buf = reinterpret_cast<S *>(a.buf) + D.pop_off;
     const PullCtx<S, T> pc = pull_ctx<S, T>(a.buf, D, g);
-    const uint32_t NP = g.NP;
     double acc[15];
 #pragma unroll
     for (int k = 0; k < 15; k++) acc[k] = 0.0;
@@ -844,7 +880,6 @@ __global__ __launch_bounds__(B) void k_links(LinkArgs a) {
     // architecture loads and stores share one wait counter, so a store issued
     // before a later load's wait would turn that wait into a write round trip.
     uint32_t links = 0;
-    uint32_t own = 0;
     S sv[2][Q];
     double rw[RAW];
     if (fluid) {
@@ -854,16 +889,16 @@ __global__ __launch_bounds__(B) void k_links(LinkArgs a) {
             if (box_nb(bb, i, Sx) >= 0 && nbr_ok(nb, i) && pnode_nb(nb, i)) links |= 1u << i;
         // plain pulls, own post-collision values (own slots are always valid,
         // so they are loaded unconditionally), own densities
-        own = pidx(p[0], p[1], p[2], g);
+        const S *own = buf + slot_at(p[0], p[1], p[2], 0, g);
         T d[2][Q];
-        pull_node(pc, own, d);
+        pull_node(pc, p[0], p[1], p[2], d);
         T fo[2][Q];
 #pragma unroll
         for (int i = 1; i < Q; i++) {
 #pragma unroll
             for (int l = 0; l < 2; l++) {
                 const T sc = Rel<S>::value ? T(wgt(i) * D.rho0[l]) : T(1);
-                fo[l][i] = ld_dev<S, T>(buf + ((uint32_t)(l * Q + i) * NP + own), sc);
+                fo[l][i] = ld_dev<S, T>(own + (l * Q + i) * g.nx, sc);
             }
         }
         const double rA = rho_n[b], rB = rho_n[S3 + b];
@@ -950,9 +985,9 @@ __global__ __launch_bounds__(B) void k_links(LinkArgs a) {
 #pragma unroll
         for (int i = 1; i < Q; i++) {
             if (!((links >> i) & 1u)) continue;
-            const uint32_t tgt = own + (uint32_t)doff(i, g);
+            S *tgt = buf + pull_slot(p[0], p[1], p[2], 0, opp(i), g);
 #pragma unroll
-            for (int l = 0; l < 2; l++) buf[(uint32_t)(l * Q + opp(i)) * NP + tgt] = sv[l][i];
+            for (int l = 0; l < 2; l++) tgt[l * Q * g.nx] = sv[l][i];
         }
 #pragma unroll
         for (int k = 0; k < RAW; k++) raw[k * S3 + b] = rw[k];
@@ -1164,7 +1199,6 @@ __global__ __launch_bounds__(B) void k_particle(ParticleArgs a) {
     double *vrho = a.vrho + D.bbox_off * 2;
     uint32_t *pmask = a.pmask + D.bbox_off;
     S *buf = reinterpret_cast<S *>(a.buf) + D.pop_off;
-    const uint32_t NP = g.NP;
 
     // 3. events and wetting layer
     double ev[20];
@@ -1308,15 +1342,14 @@ __global__ __launch_bounds__(B) void k_particle(ParticleArgs a) {
                              Un[1] + Wn[2] * rr[0] - Wn[0] * rr[2],
                              Un[2] + Wn[0] * rr[1] - Wn[1] * rr[0]};
         const double uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-        const uint32_t own = pidx(p[0], p[1], p[2], g);
         for (int i = 0; i < Q; i++) {
             const double cu = cx(i) * u[0] + cy(i) * u[1] + cz(i) * u[2];
             const double e = 1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * uu;
-            const uint32_t src = own - (uint32_t)doff(i, g);
+            S *to = buf + pull_slot(p[0], p[1], p[2], 0, i, g);
             for (int l = 0; l < 2; l++) {
                 const double wr = wgt(i) * D.rho0[l];
                 const double dev = wgt(i) * rb[l] * e - wr;
-                st_dev<S, T>(buf + ((uint32_t)(l * Q + i) * NP + src), T(dev),
+                st_dev<S, T>(to + l * Q * g.nx, T(dev),
                              Rel<S>::value ? T(1.0 / wr) : T(1));
             }
         }
@@ -1410,7 +1443,6 @@ __global__ __launch_bounds__(256) void k_init(InitArgs a) {
         philox4x32_10(c0, c1, c2, c3, D.key0, D.key1);
         const uint32_t w[2] = {c0, c1};
         S *dst = reinterpret_cast<S *>(a.buf) + D.pop_off;
-        const uint32_t own = pidx(x, y, z, g);
         const bool swap = D.init_split > 0 && z >= D.init_split;  // other phase above the split
         for (int l = 0; l < 2; l++) {
             const double base = swap ? D.rho0[1 - l] : D.rho0[l];
@@ -1419,7 +1451,7 @@ __global__ __launch_bounds__(256) void k_init(InitArgs a) {
             m[l] = rho;
             for (int i = 0; i < Q; i++) {
                 const double wr = wgt(i) * D.rho0[l];
-                st_dev<S, double>(dst + ((uint32_t)(l * Q + i) * g.NP + own - (uint32_t)doff(i, g)),
+                st_dev<S, double>(dst + pull_slot(x, y, z, l, i, g),
                                   wgt(i) * rho - wr, Rel<S>::value ? 1.0 / wr : 1.0);
             }
         }
@@ -1445,6 +1477,38 @@ __device__ __forceinline__ int solid_entry(int x, int y, int z, const RepDesc *d
     return -1;
 }
 
+// ================================================================= k_ck
+// Population part of a checkpoint: one array per component and direction over
+// the lattice padded by one layer per side, population i of node x at padded
+// position x - c_i, slot i; elements no node pulls from hold 0.  One thread per
+// padded position, consecutive ones along x.
+// Bound by HBM; the form is kept for checkpoints that outlive the process that
+// wrote them.
+template <typename S, bool SAVE>
+__global__ __launch_bounds__(256) void k_ck(CkArgs a) {
+    const int r = a.rep0 + blockIdx.y;
+    const RepDesc &D = a.desc[r];
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (D.primary != r || k >= D.ck_NP) return;
+    const Geo g = geo_of(D);
+    const int px = (int)(k % (g.nx + 2)) - 1, py = (int)(k / (g.nx + 2) % (g.ny + 2)) - 1;
+    const int pz = (int)(k / ((int64_t)(g.nx + 2) * (g.ny + 2))) - 1;
+    S *pop = reinterpret_cast<S *>(a.pop) + D.pop_off;
+    S *ck = reinterpret_cast<S *>(a.ck) + D.ck_off + k;
+#pragma unroll
+    for (int i = 0; i < Q; i++) {
+        const int x = px + cx(i), y = py + cy(i), z = pz + cz(i);
+        const bool in = x >= 0 && x < g.nx && y >= 0 && y < g.ny && z >= 0 && z < g.nz;
+        S *p = pop + (in ? pull_slot(x, y, z, 0, i, g) : 0);
+#pragma unroll
+        for (int l = 0; l < 2; l++) {
+            S *c = ck + (int64_t)(l * Q + i) * D.ck_NP;
+            if constexpr (SAVE) *c = in ? p[l * Q * g.nx] : S(0);
+            else if (in) p[l * Q * g.nx] = *c;
+        }
+    }
+}
+
 // ============================================================= k_export
 // f_{l i}(x, n) in FP64 for the nodes of planes [z_begin, z_end) of one
 // replica (particle nodes: 0).
@@ -1462,7 +1526,7 @@ __global__ __launch_bounds__(256) void k_export(ExportArgs a) {
     int b;
     const bool solid = solid_entry(x, y, z, a.desc, a.state, a.pmask, D.primary, g, b) >= 0;
     T d[2][Q];
-    if (!solid) pull_node(pc, pidx(x, y, z, g), d);
+    if (!solid) pull_node(pc, x, y, z, d);
     for (int l = 0; l < 2; l++)
         for (int i = 0; i < Q; i++)
             a.out[(int64_t)(l * Q + i) * cnt + k] =
@@ -1495,7 +1559,7 @@ __global__ __launch_bounds__(256) void k_fields_a(FieldArgs a) {
     }
     const PullCtx<S, T> pc = pull_ctx<S, T>(a.src, D, g);
     T d[2][Q];
-    pull_node(pc, pidx(x, y, z, g), d);
+    pull_node(pc, x, y, z, d);
     double jtot[3] = {0.0, 0.0, 0.0};
     for (int l = 0; l < 2; l++) {
         T rd, jl[3], mm[Q];
@@ -1564,6 +1628,13 @@ hipError_t launch_export_t(const ExportArgs &a, int64_t count, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <typename S>
+hipError_t launch_ck_t(bool save, const CkArgs &a, int blocks, int nrep, hipStream_t s) {
+    if (save) hipLaunchKernelGGL((k_ck<S, true>), dim3(blocks, nrep), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_ck<S, false>), dim3(blocks, nrep), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
 template <typename S, typename T>
 hipError_t launch_fields_a_t(const FieldArgs &a, int64_t N, hipStream_t s) {
     hipLaunchKernelGGL((k_fields_a<S, T>), dim3((int)((N + 255) / 256)), dim3(256), 0, s, a);
@@ -1586,6 +1657,9 @@ hipError_t launch_fields_a_t(const FieldArgs &a, int64_t N, hipStream_t s) {
     }                                                                                              \
     hipError_t launch_export_##SUFFIX(const ExportArgs &a, int64_t count, hipStream_t s) {         \
         return launch_export_t<S, T>(a, count, s);                                                 \
+    }                                                                                              \
+    hipError_t launch_ck_##SUFFIX(bool save, const CkArgs &a, int blocks, int nrep, hipStream_t s) { \
+        return launch_ck_t<S>(save, a, blocks, nrep, s);                                           \
     }                                                                                              \
     hipError_t launch_fields_a_##SUFFIX(const FieldArgs &a, int64_t N, hipStream_t s) {            \
         return launch_fields_a_t<S, T>(a, N, s);                                                   \

@@ -1,11 +1,12 @@
 // Device-side data layout of the library (workspace contents).
 //
-// Populations: two ping-pong buffers; replica r owns a block of 38 NP_r
-// elements laid out [component][direction][z+1][y+1][x+1] on its lattice
-// padded by one ghost layer per side (x fastest).  A buffer holds the
-// post-collision values f*_i of the last step in the slot each node pulls
-// from (slot i at padded position x - c_i); values that reach a node by
-// bounce-back or across a periodic face are written there by their
+// Populations: two ping-pong buffers; replica r owns a block of
+// 38 nx (ny + 2)(nz + 2) elements laid out [z+1][y+1][component][direction][x]
+// on its lattice with one ghost row per y side and one ghost plane per z side.
+// A buffer holds the post-collision values f*_i of the last step in the slot
+// each node pulls from (slot i at position x - c_i, x wrapped around its row;
+// the node's own slot opp(i) across an x-wall); values that reach a node by
+// bounce-back or across a periodic face in y or z are written there by their
 // producer.  Elements are stored as deviations from w_i rho0_l (FP64, FP32)
 // or as relative deviations (f - w_i rho0_l) / (w_i rho0_l) (FP16).
 #pragma once
@@ -22,8 +23,9 @@ struct RepDesc {
     int32_t nx, ny, nz;
     uint32_t walls;          // bit0 x, bit1 y, bit2 z
     int64_t N;               // nodes
-    int64_t NP;              // padded nodes (nx + 2)(ny + 2)(nz + 2)
-    int64_t pop_off;         // element offset of the replica block (38 NP) in a population buffer
+    int64_t pop_off;         // element offset of the replica block in a population buffer
+    int64_t ck_NP;           // nodes (nx + 2)(ny + 2)(nz + 2) of its block in a checkpoint
+    int64_t ck_off;          // element offset of that block (38 ck_NP)
     int32_t ty;              // rows (y) per main-kernel tile; tiles span full x rows
     int32_t nty, nchunk;     // tiles along y, z-chunks
     int32_t wg_begin;        // first main-kernel workgroup of this replica
@@ -47,7 +49,7 @@ struct RepDesc {
     uint32_t key0, key1;
     int32_t noise_diffusive, fixed_velocity;
     int32_t init_split;      // first plane of the swapped initial phase (0: none)
-    int32_t ghost_fill;      // main kernel also writes the never-pulled x-ghost slots
+    int32_t pad_fill;
     // collision coefficients and forcing in both arithmetic precisions, made
     // once on the host (kernels load them as wave-uniform values)
     Coef<float> cf32;
