@@ -101,7 +101,7 @@ __global__ __launch_bounds__(NB) void k_adj_record(RecArgs a) {
     const PullCtx<S, T> pc = pull_ctx<S, T>(a.src, D, g);
     T d[2][Q];
     pull_node(pc, x, y, z, d);
-    NodeM<T, true> m;
+    NodeM<T> m;
     node_moments(d, m);
     T *rec = static_cast<T *>(a.rec);
     const int64_t N = g.N;

@@ -496,6 +496,25 @@ size_t adj_lds_bytes(const lbm_params &q, int prec) {
     return (size_t)3 * 10 * (adj_tile_rows(q) + 2) * q.nx * (prec == LBM_FP64 ? 8 : 4);
 }
 
+// A checkpoint of the adjoint's tape: the state as it lies in the workspace
+// (read back by this context alone, in stream order).
+size_t tape_ck_bytes(lbm_ctx *c) {
+    return c->L.pop_elems * c->es + sizeof(RepState) * c->nrep + (sizeof(double) * 2 + sizeof(uint32_t)) * c->L.S3tot;
+}
+
+int tape_ck_copy(lbm_ctx *c, bool save, char *ck) {
+    const size_t bytes[4] = {c->L.pop_elems * c->es, sizeof(double) * 2 * (size_t)c->L.S3tot,
+                             sizeof(RepState) * (size_t)c->nrep, sizeof(uint32_t) * (size_t)c->L.S3tot};
+    void *live[4] = {c->d_pop(c->cur), c->d_vrho(), c->d_state(), c->d_pmask()};
+    for (int k = 0; k < 4; k++) {
+        if (!bytes[k]) continue;
+        HIP_TRY(c, hipMemcpyAsync(save ? ck : live[k], save ? live[k] : ck, bytes[k], hipMemcpyDeviceToDevice,
+                                  c->stream));
+        ck += bytes[k];
+    }
+    return LBM_OK;
+}
+
 struct AdjLayout {
     int nseg = 0, seg = 0, nwg = 0, nbw = 0, nmw = 0, lty = 0, nlt = 0;
     size_t ckb = 0, recb = 0, Ab = 0;
@@ -539,8 +558,7 @@ AdjLayout adj_plan(lbm_ctx *c, int32_t nsteps, int32_t segment) {
             if (q.walls & (1u << ax)) faces += 2 * nn[(ax + 1) % 3] * nn[(ax + 2) % 3];
         A.nmw = (int)std::max<int64_t>(1, (faces + 255) / 256);
     }
-    lbm_checkpoint_bytes(c, &A.ckb);
-    A.ckb = align_up(A.ckb);
+    A.ckb = align_up(tape_ck_bytes(c));
     A.recb = align_up(8 * N * te);
     A.Ab = align_up(8 * N * te);
     size_t o = 0;
@@ -1235,11 +1253,11 @@ int adjoint_forward(lbm_ctx *c, int32_t nsteps, int32_t segment, void *dev_adj, 
     auto seg_len = [&](int s) { return std::min(A.seg, nsteps - s * A.seg); };
     RepState *rst = reinterpret_cast<RepState *>(w + A.rst);
     for (int s = 0; s < A.nseg; s++) {
-        if ((rc = lbm_checkpoint(c, ck(s))) != LBM_OK) return rc;
+        if ((rc = tape_ck_copy(c, true, ck(s))) != LBM_OK) return rc;
         rc = s + 1 < A.nseg ? lbm_step(c, seg_len(s)) : record_segment(c, A, w, rst, seg_len(s));
         if (rc != LBM_OK) return rc;
     }
-    if ((rc = lbm_checkpoint(c, ck(A.nseg))) != LBM_OK) return rc;
+    if ((rc = tape_ck_copy(c, true, ck(A.nseg))) != LBM_OK) return rc;
     RepState st1;
     if ((rc = read_state(c, 0, &st1)) != LBM_OK) return rc;
     if (J) *J = (st1.uz_sum - st0.uz_sum) / nsteps;
@@ -1312,7 +1330,7 @@ int adjoint_backward(lbm_ctx *c, double grad[5], double *J) {
     for (int s = A.nseg - 1; s >= 0; s--) {
         const int K = seg_len(s);
         if (s + 1 < A.nseg) {  // replay (the last segment was recorded by the sweep)
-            if ((rc = lbm_restore(c, ck(s))) != LBM_OK) return rc;
+            if ((rc = tape_ck_copy(c, false, ck(s))) != LBM_OK) return rc;
             if ((rc = record_segment(c, A, w, rst, K)) != LBM_OK) return rc;
         }
         for (int k = K - 1; k >= 0; k--) {
@@ -1340,7 +1358,7 @@ int adjoint_backward(lbm_ctx *c, double grad[5], double *J) {
             an = 1 - an;
         }
     }
-    if ((rc = lbm_restore(c, ck(A.nseg))) != LBM_OK) return rc;
+    if ((rc = tape_ck_copy(c, false, ck(A.nseg))) != LBM_OK) return rc;
     AdjState h;
     HIP_TRY(c, hipMemcpyAsync(&h, w + A.adj, sizeof(AdjState), hipMemcpyDeviceToHost, c->stream));
     RepState st1;

@@ -228,9 +228,9 @@ __device__ __forceinline__ void buf_st(S v, Rsrc r, uint32_t vo, uint32_t so) {
 // scalar registers do not hold every derived offset at once)
 __device__ __forceinline__ void renew(int32_t &v) { asm volatile("" : "+s"(v)); }
 
-// z uniform over the wave; (x, y) per lane
-template <typename S, typename T>
-__device__ __forceinline__ void pull_row(PullCtx<S, T> c, int x, int y, int z, T (&d)[2][Q]) {
+// Components L0 .. L0 + NL - 1 of a node; z uniform over the wave, (x, y) per lane.
+template <int NL, typename S, typename T>
+__device__ __forceinline__ void pull_row(PullCtx<S, T> c, int x, int y, int z, int L0, T (&d)[NL][Q]) {
     constexpr uint32_t es = sizeof(S);
     renew(c.nx);
     renew(c.RS);
@@ -254,11 +254,12 @@ __device__ __forceinline__ void pull_row(PullCtx<S, T> c, int x, int y, int z, T
                                (cz(i) > 0 ? PSb : 0u);
             vo = (cx(i) > 0 ? wm : wp) ? own + k : vo;
         }
-        const uint32_t so = (uint32_t)(1 - cy(i)) * RSb + (uint32_t)i * nxb;
-        const Rsrc r = cz(i) > 0 ? r1 : r0;
-        const S a = buf_ld<S>(r, vo, so), b = buf_ld<S>(r, vo, so + (uint32_t)Q * nxb);
-        d[0][i] = ld_dev<S, T>(&a, w * c.scale[0]);
-        d[1][i] = ld_dev<S, T>(&b, w * c.scale[1]);
+        const uint32_t so = (uint32_t)(1 - cy(i)) * RSb + (uint32_t)(L0 * Q + i) * nxb;
+#pragma unroll
+        for (int l = 0; l < NL; l++) {
+            const S v = buf_ld<S>(cz(i) > 0 ? r1 : r0, vo, so + (uint32_t)(l * Q) * nxb);
+            d[l][i] = ld_dev<S, T>(&v, w * (L0 + l ? c.scale[1] : c.scale[0]));
+        }
     }
 }
 
@@ -278,33 +279,26 @@ __device__ __forceinline__ void pull_node(const PullCtx<S, T> &c, int x, int y, 
     }
 }
 
-// What a collision needs from the pulled populations of a node: density
-// deviations, momenta and (unless every relaxation time is 1, when the
-// post-collision state depends on density and momentum only) modes 4..18.
-template <typename T, bool TAU1>
+// Density deviations and momenta of the pulled populations of a node.
+template <typename T>
 struct NodeM {
     T rd[2];
     T j[2][3];
-    T m[2][TAU1 ? 1 : Q];
 };
 
-template <typename T, bool TAU1>
-__device__ __forceinline__ void node_moments(const T (&d)[2][Q], NodeM<T, TAU1> &s) {
+template <typename T>
+__device__ __forceinline__ void node_moments(const T (&d)[2][Q], NodeM<T> &s) {
 #pragma unroll
     for (int l = 0; l < 2; l++) {
-        if constexpr (TAU1) {
-            T r = T(0), jx = T(0), jy = T(0), jz = T(0);
+        T r = T(0), jx = T(0), jy = T(0), jz = T(0);
 #pragma unroll
-            for (int i = 0; i < Q; i++) {
-                r += d[l][i];
-                if (cx(i) > 0) jx += d[l][i]; else if (cx(i) < 0) jx -= d[l][i];
-                if (cy(i) > 0) jy += d[l][i]; else if (cy(i) < 0) jy -= d[l][i];
-                if (cz(i) > 0) jz += d[l][i]; else if (cz(i) < 0) jz -= d[l][i];
-            }
-            s.rd[l] = r; s.j[l][0] = jx; s.j[l][1] = jy; s.j[l][2] = jz;
-        } else {
-            component_modes(d[l], s.rd[l], s.j[l], s.m[l]);
+        for (int i = 0; i < Q; i++) {
+            r += d[l][i];
+            if (cx(i) > 0) jx += d[l][i]; else if (cx(i) < 0) jx -= d[l][i];
+            if (cy(i) > 0) jy += d[l][i]; else if (cy(i) < 0) jy -= d[l][i];
+            if (cz(i) > 0) jz += d[l][i]; else if (cz(i) < 0) jz -= d[l][i];
         }
+        s.rd[l] = r; s.j[l][0] = jx; s.j[l][1] = jy; s.j[l][2] = jz;
     }
 }
 
@@ -403,7 +397,7 @@ constexpr bool main_unroll = sizeof(T) == 4 && TAU1;
 // (products with zero).  Without it no normals are drawn.  Being a compile-
 // time choice, the noise-free form costs the noisy one nothing.
 template <typename S, typename T, int B, bool TAU1, bool GROUP, bool NOISE>
-__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(main_fast_form<S, T, TAU1> ? 4 : 1)))
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(main_fast_form<S, T, TAU1> ? 4 : sizeof(T) == 4 ? 3 : 2)))
 void k_main(MainArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     T *lds = reinterpret_cast<T *>(smem);
@@ -456,7 +450,7 @@ void k_main(MainArgs a) {
     // density deviation of a box node: pulled (plus the mass correction), or
     // the wetting-layer value on particle nodes; fluid nodes also return
     // their moments
-    auto node_density = [&](int xx, int yy, int zz, NodeM<T, TAU1> &s, T &rA, T &rB) -> bool {
+    auto node_density = [&](int xx, int yy, int zz, NodeM<T> &s, T &rA, T &rB) -> bool {
         int b = -1;
         if (hp) b = bbox_index(xx, yy, zz, org, Sx, g);
         if (b < 0 || !(pmask[b] & MASK_SOLID)) {
@@ -479,7 +473,7 @@ void k_main(MainArgs a) {
             }
             if (vi < 0) {
                 T d[2][Q];
-                pull_row(pcl, xx, yy, zz, d);
+                pull_row<2>(pcl, xx, yy, zz, 0, d);
                 node_moments(d, s);
                 s.rd[0] += dl[0];
                 s.rd[1] += dl[1];
@@ -496,7 +490,7 @@ void k_main(MainArgs a) {
         return false;
     };
 
-    NodeM<T, TAU1> nxt;
+    NodeM<T> nxt;
     bool nxt_fluid = false;
 
     // fill LDS plane zp (unmapped index); the interior node's moments go to nxt
@@ -513,7 +507,7 @@ void k_main(MainArgs a) {
             const int row = h < nx ? -1 : rows;
             const int xx = h < nx ? h : h - nx;
             const int yy = mirror1(y0 + row, g.ny, g.wy);
-            NodeM<T, TAU1> hd;
+            NodeM<T> hd;
             T rA, rB;
             node_density(xx, yy, zz, hd, rA, rB);
             L(zp, 0, row, xx) = rA;
@@ -541,7 +535,7 @@ void k_main(MainArgs a) {
         // hoisted as lane masks that would crowd the scalar registers
         asm volatile("" : "+v"(xyface));
         const int zp = zfirst + dir * k;
-        const NodeM<T, TAU1> cur = nxt;
+        const NodeM<T> cur = nxt;
         const bool cur_fluid = nxt_fluid;
         fill(zp);
         __syncthreads();
@@ -610,6 +604,14 @@ void k_main(MainArgs a) {
                 const T Fl[3] = {l ? F[1][0] : F[0][0], l ? F[1][1] : F[0][1], l ? F[1][2] : F[0][2]};
                 const T r0l = l ? cf.rho0[1] : cf.rho0[0];
                 const T sig = l ? T(-1) : T(1);
+                // general relaxation: modes 4..18 of the populations, pulled once more
+                // (from the caches); carried along since the fill they cost 30
+                // registers.  The loads are issued before the normals are drawn.
+                T dl1[1][TAU1 ? 1 : Q];
+                if constexpr (!TAU1) {
+                    pull_row<1>(pcl, x, y, z, l, dl1);
+                    if constexpr (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
+                }
                 T zl[16];
                 if constexpr (NOISE) {
 #pragma unroll
@@ -623,9 +625,8 @@ void k_main(MainArgs a) {
                 if constexpr (TAU1) {
                     relax_tau1(r0l, sig, rdl, jl, Fl, u, xid, zl, cf, out);
                 } else {
-                    T ml[Q];
-#pragma unroll
-                    for (int k = 4; k < Q; k++) ml[k] = l ? cur.m[1][k] : cur.m[0][k];
+                    T ml[Q], rdm, jm[3];
+                    component_modes(dl1[0], rdm, jm, ml);
                     relax_component(r0l, sig, rdl, jl, ml, Fl, u, xid, zl, cf, out);
                 }
                 const T sc = Rel<S>::value ? r0l : T(1);
@@ -938,7 +939,7 @@ __global__ __launch_bounds__(B) void k_links(LinkArgs a) {
             acc[5] += dd[0] * P[1] - dd[1] * P[0];
         }
         // densities and momentum of step n+1 at this node
-        NodeM<T, true> m;
+        NodeM<T> m;
         node_moments(d, m);
         rw[0] = D.rho0[0] + (double)m.rd[0];
         rw[1] = D.rho0[1] + (double)m.rd[1];

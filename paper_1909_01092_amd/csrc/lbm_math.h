@@ -67,9 +67,18 @@ __host__ __device__ inline void box_muller(uint32_t w1, uint32_t w2, double &z0,
     const double u1 = ((double)w1 + 0.5) * 0x1p-32;
     const double u2 = ((double)w2 + 0.5) * 0x1p-32;
     const double r = sqrt(-2.0 * log(u1));
+#if defined(__HIP_DEVICE_COMPILE__)
+    // angle in half turns (2 u2 is exact): no argument reduction by pi, and one
+    // call for both
+    double s, c;
+    sincospi(2.0 * u2, &s, &c);
+    z0 = r * c;
+    z1 = r * s;
+#else
     const double a = 2.0 * 3.14159265358979323846 * u2;
     z0 = r * cos(a);
     z1 = r * sin(a);
+#endif
 }
 
 // FP32 form.  ln u1 keeps full relative accuracy for u1 near 1: with
