@@ -35,8 +35,7 @@ void *g_scratch_ptr[MAX_DEVICES] = {};
 constexpr size_t ALIGN = 256;
 constexpr int MAIN_BLOCK_MIN = 256;
 constexpr size_t MAIN_LDS_MAX = 64 * 1024;
-constexpr int K3_BLOCK = K3_THREADS;
-constexpr int K3_FINISH_APART = 256;  // particle workgroups above which k_finish runs apart
+constexpr int K3_BLOCK = K3_NODES;
 constexpr int INIT_BLOCK = 256;
 
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
@@ -63,7 +62,7 @@ void init_org(const lbm_params &q, int32_t org[3]) {
 }
 
 struct Layout {
-    size_t tables, desc, state, pop[2], part1, part3, raw, vrho, rho_n, pmask, series, aux, total;
+    size_t tables, desc, state, pop[2], part1, part3, raw, vrho, rho_n, pmask[2], series, aux, total;
     std::vector<int64_t> pop_off, ck_off, bbox_off, part3_off, series_off, init_wg;
     std::vector<int> S, k3_count;
     int64_t Ntot = 0, pop_elems = 0, ck_elems = 0, ck_max = 0, S3tot = 0, part3_tot = 0, series_tot = 0, init_tot = 0;
@@ -122,7 +121,7 @@ Layout plan(const Groups &G, int prec) {
     L.raw = take(sizeof(double) * std::max<int64_t>(RAW * L.S3tot, 1));
     L.vrho = take(sizeof(double) * std::max<int64_t>(2 * L.S3tot, 1));
     L.rho_n = take(sizeof(double) * std::max<int64_t>(2 * L.S3tot, 1));
-    L.pmask = take(sizeof(uint32_t) * std::max<int64_t>(L.S3tot, 1));
+    for (size_t &m : L.pmask) m = take(sizeof(uint32_t) * std::max<int64_t>(L.S3tot, 1));
     L.series = take(sizeof(double) * std::max<int64_t>(L.series_tot, 1));
     L.aux = take(sizeof(double) * L.aux_doubles);
     L.total = o;
@@ -254,6 +253,7 @@ struct lbm_ctx {
     int tau1 = 0;
     int noise = 0;            // some replica has kT > 0
     int groups = 0;           // some fluid holds several spheres
+    int spheres = 0;          // some replica holds a sphere
     int graph_steps = 0, graph_parity = -1;
     hipGraphExec_t gexec = nullptr;
     bool timing = false;
@@ -280,7 +280,10 @@ struct lbm_ctx {
     double *d_raw() { return reinterpret_cast<double *>(ws + L.raw); }
     double *d_vrho() { return reinterpret_cast<double *>(ws + L.vrho); }
     double *d_rho_n() { return reinterpret_cast<double *>(ws + L.rho_n); }
-    uint32_t *d_pmask() { return reinterpret_cast<uint32_t *>(ws + L.pmask); }
+    // node masks of the current step; the particle kernel reads these and writes
+    // the next step's into the other array
+    uint32_t *d_pmask(int k) { return reinterpret_cast<uint32_t *>(ws + L.pmask[k]); }
+    uint32_t *d_pmask() { return d_pmask(cur); }
     double *d_series() { return reinterpret_cast<double *>(ws + L.series); }
     double *d_aux() { return reinterpret_cast<double *>(ws + L.aux); }
 };
@@ -431,11 +434,12 @@ int enqueue_step(lbm_ctx *c, bool timed, const StepScratch &sc) {
     la.k3_begin = c->d_tables() + (c->nrep + 1);
     la.nrep = c->nrep;
     la.buf = c->d_pop(1 - c->cur);
+    la.pmask = c->d_pmask();
     la.vrho = c->d_vrho();
     la.rho_n = sc.rho_n;
     la.raw = sc.raw;
     la.part1 = sc.part1;
-    e = launch_links(c->prec, la, c->k3_grid, c->stream);
+    if (c->spheres) e = launch_links(c->prec, la, c->k3_grid, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "link kernel launch");
     ParticleArgs pa;
     pa.desc = c->d_desc();
@@ -445,15 +449,11 @@ int enqueue_step(lbm_ctx *c, bool timed, const StepScratch &sc) {
     pa.buf = c->d_pop(1 - c->cur);
     pa.part1 = sc.part1;
     pa.part3 = sc.part3;
-    pa.pmask = c->d_pmask();
+    pa.pmask_old = c->d_pmask(c->cur);
+    pa.pmask = c->d_pmask(1 - c->cur);
     pa.raw = sc.raw;
     pa.vrho = c->d_vrho();
     pa.series = c->d_series();
-    // many particle workgroups: a separate finishing launch beats one
-    // device-scope fence per workgroup (192-replica ensemble: 4.02 against
-    // 4.30 ms per step); few: the fences are cheaper than the extra launch
-    // (64x64x256 channel, 168 workgroups: 0.1365 against 0.1403 ms per step)
-    pa.finish_apart = c->k3_grid > K3_FINISH_APART ? 1 : 0;
     e = launch_particle(c->prec, pa, c->k3_grid, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "particle kernel launch");
     c->cur = 1 - c->cur;
@@ -643,6 +643,7 @@ LBM_API int lbm_init(const lbm_params *p_in, int32_t n_replicas, int32_t precisi
         D.pop_off = L.pop_off[r];
         D.S = L.S[r];
         D.has_particle = has_sphere(q);
+        c->spheres = c->spheres || D.has_particle;
         D.bbox_off = L.bbox_off[r];
         D.part3_off = L.part3_off[r];
         D.series_off = L.series_off[r];

@@ -28,17 +28,17 @@ struct LinkArgs {
     const int32_t *k3_begin;
     int32_t nrep;
     void *buf;                 // post-collision populations of step n (bounced values written)
+    const uint32_t *pmask;     // node masks of step n (bbox)
     const double *vrho;        // wetting-layer densities of step n (bbox)
     const double *rho_n;       // densities of step n (bbox)
     double *raw;               // post-streaming densities and momenta of fluid box nodes, written
     double *part1;             // per-workgroup link partials
 };
 
-// Threads per workgroup of the bounding-box kernels k_links / k_particle: one
-// wave.  The box chain is latency-bound on a few thousand nodes, so more,
-// smaller workgroups spread it over more CUs (64x64x256 channel: 0.1365
-// against 0.1394 ms per step with 256 threads).
-constexpr int K3_THREADS = 64;
+// Box nodes per workgroup of the bounding-box kernels k_links / k_particle, and
+// its threads (four per node).
+constexpr int K3_NODES = 64;
+constexpr int K3_THREADS = 4 * K3_NODES;
 
 struct ParticleArgs {
     const RepDesc *desc;
@@ -48,11 +48,11 @@ struct ParticleArgs {
     void *buf;                 // populations of step n+1 (uncovered-node values written)
     const double *part1;       // link partials
     double *part3;             // cover / uncover partials
+    const uint32_t *pmask_old; // node masks of step n
     uint32_t *pmask;           // node masks of step n+1, written
     const double *raw;
     double *vrho;              // wetting-layer densities of step n+1, written
     double *series;
-    int32_t finish_apart;      // 1: k_finish publishes the step; 0: the last workgroup does
 };
 
 struct InitArgs {

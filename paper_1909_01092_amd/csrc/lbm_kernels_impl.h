@@ -37,6 +37,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "lbm_kernels.h"
 #include "lbm_math.h"
 #include "lbm_types.h"
@@ -749,37 +751,6 @@ __device__ __forceinline__ bool nbr_ok(const Nbr &nb, int i) { return (nb.ok >> 
 
 __device__ __forceinline__ bool pnode_nb(const Nbr &nb, int i) { return (nb.solid >> i) & 1u; }
 
-// box coordinates of lattice node p in the box at org (periodic axes
-// unwrapped next to it); false when p lies outside the box
-__device__ __forceinline__ bool box_coords(const int (&p)[3], const int32_t *org, int S, const Geo &g,
-                                           int (&bb)[3]) {
-    const int n3[3] = {g.nx, g.ny, g.nz};
-    const bool w3[3] = {g.wx, g.wy, g.wz};
-    bool in = true;
-#pragma unroll
-    for (int ax = 0; ax < 3; ax++) {
-        int v = p[ax] - org[ax];
-        if (!w3[ax]) { if (v < 0) v += n3[ax]; else if (v >= n3[ax]) v -= n3[ax]; }
-        bb[ax] = v;
-        in = in && v >= 0 && v < S;
-    }
-    return in;
-}
-
-// box index of neighbour p + c_i from p's box coordinates; -1 outside the box
-__device__ __forceinline__ int box_nb(const int (&bb)[3], int i, int S) {
-    const int qx = bb[0] + cx(i), qy = bb[1] + cy(i), qz = bb[2] + cz(i);
-    if (qx < 0 || qy < 0 || qz < 0 || qx >= S || qy >= S || qz >= S) return -1;
-    return (qz * S + qy) * S + qx;
-}
-
-// lattice position of neighbour p + c_i (wrapped on periodic axes)
-__device__ __forceinline__ void nb_pos(const int (&p)[3], int i, const Geo &g, int (&q)[3]) {
-    q[0] = mirror1(p[0] + cx(i), g.nx, false);
-    q[1] = mirror1(p[1] + cy(i), g.ny, false);
-    q[2] = mirror1(p[2] + cz(i), g.nz, false);
-}
-
 // storage form of a deviation (as st_dev writes it) and the value a pull of
 // it returns (as ld_dev reads it with the pull's scale)
 template <typename S, typename T>
@@ -793,219 +764,353 @@ __device__ __forceinline__ T store_round(double v, T inv_scale, T scale, S &sv) 
     }
 }
 
-// Mean post-streaming density of the neighbours of p that are fluid at X^n
-// and at X^{n+1} (raw of the box at orgo); rho0 when there is none.  Every
-// argument is passed by value, so that no caller keeps its locals in scratch
-// memory for the call.
-struct Rho2 {
-    double a, b;
+// Four lanes per box node.  k_links and k_particle are chains of a few
+// thousand nodes on a chip of 1024 SIMDs, so what they take is the number of
+// instructions one wave issues, one after another, and the round trips it
+// waits for.  Lane q of a node's quad takes the directions i = 5 q + m,
+// m = 0 .. 4 (i = 19: none): a quarter of the loads, predicates and link terms
+// each, in code that is the same for every direction (the velocities come from
+// bit tables) and a fifth as long.  With one lane per node every surface wave
+// issued 1.7 k (k_links) and 2.2 k (k_particle) vector instructions.
+// 64 x 64 x 256 channel (R = 8): k_links 12.6 -> 6.8 us, k_particle 23.3 -> 16 us;
+// 16 x 16 x 32 (R = 3): 11.7 -> 5.7 and 16.8 -> 10.7 us.  192 spheres, where the
+// chip is full and the quads' common work counts: both together 145 -> 175 us of
+// a 2.7 ms step.
+constexpr int QM = 5;
+constexpr uint32_t dir_bits(int ax, int m) {  // c + 1 of the four directions 5 q + m, two bits each
+    uint32_t v = 0;
+    for (int q = 0; q < 4; q++) {
+        const int i = QM * q + m;
+        const int c = i >= Q ? 0 : ax == 0 ? cx(i) : ax == 1 ? cy(i) : cz(i);
+        v |= (uint32_t)(c + 1) << (2 * q);
+    }
+    return v;
+}
+struct QDir {
+    int c[3];
+    int i, io;      // direction and its opposite
+    bool valid;     // a moving direction (i = 1 .. 18)
 };
-struct Pos3 {
-    double v[3];
-};
-struct Org3 {
-    int32_t v[3];
-};
+template <int M>
+__device__ __forceinline__ QDir quad_dir(int q) {
+    QDir d;
+    constexpr uint32_t bx = dir_bits(0, M), by = dir_bits(1, M), bz = dir_bits(2, M);
+    d.c[0] = (int)((bx >> (2 * q)) & 3u) - 1;
+    d.c[1] = (int)((by >> (2 * q)) & 3u) - 1;
+    d.c[2] = (int)((bz >> (2 * q)) & 3u) - 1;
+    d.i = QM * q + M;
+    d.io = (d.i & 1) ? d.i + 1 : d.i - 1;
+    if (M == 0 && q == 0) d.io = 0;
+    d.valid = M == 0 ? q != 0 : M == QM - 1 ? q != 3 : true;
+    return d;
+}
+// the direction against d
+__device__ __forceinline__ QDir against(const QDir &d) {
+    return {{-d.c[0], -d.c[1], -d.c[2]}, d.io, d.i, d.valid};
+}
+// w_i of direction 5 q + M
+template <int M>
+__device__ __forceinline__ double quad_w(int q) {
+    if (M == 0) return q == 0 ? 1.0 / 3.0 : q == 1 ? 1.0 / 18.0 : 1.0 / 36.0;
+    if (M == 1) return q <= 1 ? 1.0 / 18.0 : 1.0 / 36.0;
+    return q == 0 ? 1.0 / 18.0 : 1.0 / 36.0;
+}
+// f(integral_constant<int, m>) for m = 0 .. 4
+template <typename F>
+__device__ __forceinline__ void for_quad_dirs(F &&f) {
+    f(std::integral_constant<int, 0>{});
+    f(std::integral_constant<int, 1>{});
+    f(std::integral_constant<int, 2>{});
+    f(std::integral_constant<int, 3>{});
+    f(std::integral_constant<int, 4>{});
+}
 
-__device__ __forceinline__ Rho2 mean_kept(int px, int py, int pz, Pos3 Xo, Pos3 Xn, double R2,
-                                        const double *raw, Org3 orgo, int Sx, int S3, Geo g,
-                                        double rho0A, double rho0B) {
-    const int p[3] = {px, py, pz};
-    Nbr no, nn;
-    nbr_of(p, Xo.v, R2, g, no);
-    nbr_of(p, Xn.v, R2, g, nn);
-    int bo[3];
-    const bool inbox = box_coords(p, orgo.v, Sx, g, bo);
-    int idx[Q];
-    uint32_t keep = 0;
+// sum over the quad, the same bits in its four lanes
+__device__ __forceinline__ int quad_sum(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, false);
+    return x;
+}
+__device__ __forceinline__ uint32_t quad_or(uint32_t x) {
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, false);
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, false);
+    return x;
+}
+// the value of lane SRC of the quad
+template <int SRC>
+__device__ __forceinline__ float quad_bcast(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), SRC * 0x55, 0xf, 0xf, false));
+}
+template <int SRC>
+__device__ __forceinline__ double quad_bcast(double x) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), SRC * 0x55, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(x), SRC * 0x55, 0xf, 0xf, false));
+}
+
+// sum of a node's 20 values (5 per lane) in the order of its directions, in
+// every lane: lane 0 adds its five, lane 1 goes on from there, ...
+__device__ __forceinline__ double chain_sum(const double (&v)[QM]) {
+    double x = 0.0;
+    auto five = [&] {
 #pragma unroll
-    for (int i = 1; i < Q; i++) {
-        idx[i] = inbox ? box_nb(bo, i, Sx) : -1;
-        if (idx[i] >= 0 && nbr_ok(no, i) && !pnode_nb(no, i) && !pnode_nb(nn, i))
-            keep |= 1u << i;
-    }
-    double s0 = 0.0, s1 = 0.0;
+        for (int m = 0; m < QM; m++) x += v[m];
+    };
+    five();
+    x = quad_bcast<0>(x);
+    five();
+    x = quad_bcast<1>(x);
+    five();
+    x = quad_bcast<2>(x);
+    five();
+    return quad_bcast<3>(x);
+}
+
+// Box node b of the box at org (edge S): its box coordinates and lattice
+// position; false beyond the box or in a wall layer.  The box starts less than
+// one period before the lattice and is no longer than one.
+__device__ __forceinline__ bool box_node(int b, const int32_t *org, int S, const Geo &g, int (&bb)[3], int (&p)[3]) {
+    const uint32_t ub = (uint32_t)b, uS = (uint32_t)S;
+    const uint32_t row = ub / uS;
+    bb[0] = (int)(ub - row * uS);
+    bb[2] = (int)(row / uS);
+    bb[1] = (int)(row - (uint32_t)bb[2] * uS);
+    const int n3[3] = {g.nx, g.ny, g.nz};
+    const bool w3[3] = {g.wx, g.wy, g.wz};
+    bool in = bb[2] < S;
 #pragma unroll
-    for (int i = 1; i < Q; i++) {
-        if (!((keep >> i) & 1u)) continue;
-        s0 += raw[idx[i]];
-        s1 += raw[S3 + idx[i]];
+    for (int a = 0; a < 3; a++) {
+        int v = org[a] + bb[a];
+        if (v < 0 || v >= n3[a]) {
+            if (w3[a]) in = false;
+            else v = v < 0 ? v + n3[a] : v - n3[a];
+        }
+        p[a] = v;
     }
-    const int cnt = __builtin_popcount(keep);
-    Rho2 rb;
-    rb.a = cnt > 0 ? s0 / cnt : rho0A;
-    rb.b = cnt > 0 ? s1 / cnt : rho0B;
-    return rb;
+    return in;
+}
+
+// lattice position p + c; false across a wall
+__device__ __forceinline__ bool step_to(const int (&p)[3], const int (&c)[3], const Geo &g, int (&q)[3]) {
+    bool ok = true;
+    const int n3[3] = {g.nx, g.ny, g.nz};
+    const bool w3[3] = {g.wx, g.wy, g.wz};
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        int v = p[a] + c[a];
+        if (v < 0 || v >= n3[a]) {
+            if (w3[a]) ok = false;
+            v = v < 0 ? v + n3[a] : v - n3[a];
+        }
+        q[a] = v;
+    }
+    return ok;
+}
+
+// box index of box coordinates bb + c, -1 outside the box
+__device__ __forceinline__ int box_at(const int (&bb)[3], const int (&c)[3], int S) {
+    const int x = bb[0] + c[0], y = bb[1] + c[1], z = bb[2] + c[2];
+    const bool in = (uint32_t)x < (uint32_t)S && (uint32_t)y < (uint32_t)S && (uint32_t)z < (uint32_t)S;
+    return in ? (z * S + y) * S + x : -1;
+}
+
+// element offset, from the node's own row (slot 0 at its x), of the slot it
+// pulls direction d from (component A): pull_slot with a direction per lane
+__device__ __forceinline__ int pull_off(int x, const QDir &d, const Geo &g) {
+    const int sx = x - d.c[0];
+    const bool out = sx < 0 || sx >= g.nx;
+    const int wr = sx < 0 ? g.nx : (out ? -g.nx : 0);
+    const int off = d.i * g.nx - d.c[1] * row_stride(g) - d.c[2] * plane_stride(g) - d.c[0] + wr;
+    return (out && g.wx) ? d.io * g.nx : off;
+}
+
+// Sum of 64 numbers v[0 .. 63] by the 16 threads s = 0 .. 15 of a DPP row, as
+// the balanced tree of neighbouring pairs (the tree of wave_sum); the result is
+// in each of them.
+__device__ __forceinline__ double row_sum64(const double *v, int s) {
+    double x = (v[4 * s] + v[4 * s + 1]) + (v[4 * s + 2] + v[4 * s + 3]);
+    x = dpp_add<0xB1>(x);
+    x = dpp_add<0x4E>(x);
+    x = dpp_add<0x141>(x);
+    return dpp_add<0x140>(x);
 }
 
 // =============================================================== k_links
-// One thread per node of the box of X^n.  A node p fluid at X^n with links
+// Four lanes per node of the box of X^n.  A node p fluid at X^n with links
 // to the sphere (p + c_i a particle node) applies the moving-wall
 // bounce-back f_opp(i)(p) = f*_i(p) - 6 w_i rho_l(p) (c_i . u_b), u_b the
 // rigid velocity at the link midpoint, and writes it into the slot p pulls
 // from (opp(i) at p + c_i) for the next step; it sums the exchanged momentum
 // sum_l (2 f*_i - 6 w_i rho_l c_i . u_b) c_i and its torque about X^n, the
 // bounce-back mass flux and the reaction of the wetting layer on the sphere.
-// Every fluid box node then forms its step-(n+1) populations (plain pulls,
-// its own bounced values on links) and stores their densities and momentum
-// for the particle kernel.  Per-workgroup FP64 sums, fixed order.
-template <typename S, typename T, int B>
-__global__ __launch_bounds__(B) void k_links(LinkArgs a) {
-    __shared__ double red[(B / 64) * 16];
+// Every fluid node near the sphere then forms its step-(n+1) populations
+// (plain pulls, its own bounced values on links) and stores their densities
+// and momentum for the particle kernel, which reads them within sqrt(2) of
+// particle nodes at X^n or X^{n+1} (|U| < 1/2 per axis): nodes beyond R + 3 do
+// nothing.  Particle nodes are read from the flags k_particle left.
+// Every load is issued before the first is used (no load depends on a flag).
+template <typename S, typename T>
+__global__ __launch_bounds__(K3_THREADS) void k_links(LinkArgs a) {
+    __shared__ double red[15 * K3_NODES];
     const int r = find_rep(a.k3_begin, a.nrep, blockIdx.x);
-    const RepDesc *__restrict__ dp = a.desc + r;  // read-only in this kernel
-    const RepDesc &D = *dp;
-    const RepState st = a.state[r];
+    const RepDesc &D = a.desc[r];
+    const RepState &st = a.state[r];
     if (!D.has_particle) return;
     const Geo g = geo_of(D);
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, q = t & 3;
     const int local = blockIdx.x - D.k3_begin;
     const int Sx = D.S, S3 = Sx * Sx * Sx;
     const int32_t org[3] = {st.org[0], st.org[1], st.org[2]};
-    const double X[3] = {st.X[0], st.X[1], st.X[2]};
+    const double X[3] = {st.X[0], st.X[1], st.X[2]}, U[3] = {st.U[0], st.U[1], st.U[2]};
+    const double W[3] = {st.W[0], st.W[1], st.W[2]};
+    const double dlt[2] = {st.delta[0], st.delta[1]};
+    const double rho0[2] = {D.rho0[0], D.rho0[1]};
     const double *vrho = a.vrho + D.bbox_off * 2;
     const double *rho_n = a.rho_n + D.bbox_off * 2;
+    const uint32_t *pmask = a.pmask + D.bbox_off;
     double *raw = a.raw + D.bbox_off * RAW;
     S *buf = reinterpret_cast<S *>(a.buf) + D.pop_off;
-    const PullCtx<S, T> pc = pull_ctx<S, T>(a.buf, D, g);
-    double acc[15];
-#pragma unroll
-    for (int k = 0; k < 15; k++) acc[k] = 0.0;
-    const int b = local * B + t;
+    const int b = local * K3_NODES + (t >> 2);
     int bb[3], p[3];
-    const bool in = b < S3 && bbox_pos(b, org, Sx, g, bb, p);
-    Nbr nb;
-    nbr_of(p, X, D.R2, g, nb);
-    const bool fluid = in && !pnode_nb(nb, 0);
-    // Loads, arithmetic and stores are kept in three separate phases: on this
-    // architecture loads and stores share one wait counter, so a store issued
-    // before a later load's wait would turn that wait into a write round trip.
-    uint32_t links = 0;
-    S sv[2][Q];
-    double rw[RAW];
-    if (fluid) {
-        // fluid node: links to neighbours that are particle nodes at X^n
-#pragma unroll
-        for (int i = 1; i < Q; i++)
-            if (box_nb(bb, i, Sx) >= 0 && nbr_ok(nb, i) && pnode_nb(nb, i)) links |= 1u << i;
-        // plain pulls, own post-collision values (own slots are always valid,
-        // so they are loaded unconditionally), own densities
-        const S *own = buf + slot_at(p[0], p[1], p[2], 0, g);
-        T d[2][Q];
-        pull_node(pc, p[0], p[1], p[2], d);
-        T fo[2][Q];
-#pragma unroll
-        for (int i = 1; i < Q; i++) {
+    const bool in = box_node(b, org, Sx, g, bb, p);
+    const double dd[3] = {sepd(p[0] - X[0], g.nx, g.wx), sepd(p[1] - X[1], g.ny, g.wy),
+                          sepd(p[2] - X[2], g.nz, g.wz)};
+    const double far = D.radius + 3.0;
+    const bool near = in && dd[0] * dd[0] + dd[1] * dd[1] + dd[2] * dd[2] < far * far;
+    double vec[3] = {0.0, 0.0, 0.0}, mass[2] = {0.0, 0.0};
+    int nlinks = 0;
+    bool solid = false;
+    if (near) {
+        const int64_t own = slot_at(p[0], p[1], p[2], 0, g);
+        const S *row = buf + own;
+        const double rl[2] = {rho_n[b], rho_n[S3 + b]}, vw[2] = {vrho[b], vrho[S3 + b]};
+        solid = pmask[b] & MASK_SOLID;
+        // per direction i of this lane: the neighbour p + c_i, the population pulled
+        // from it (direction opp(i)) and the node's own post-collision value
+        // leaving along c_i
+        S dv[2][QM], fv[2][QM];
+        uint32_t pm[QM];
+        double rn[2][QM];             // densities of the neighbours
+        bool ok[QM];
+        for_quad_dirs([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            const QDir d = quad_dir<m>(q);
+            const int off = d.i < Q ? pull_off(p[0], against(d), g) : 0;
+            const int ownoff = d.i < Q ? d.i * g.nx : 0;
+            int np[3];
+            const int nbi = box_at(bb, d.c, Sx);
+            ok[m] = d.valid && nbi >= 0 && step_to(p, d.c, g, np);
+            const int nb = nbi >= 0 ? nbi : b;
 #pragma unroll
             for (int l = 0; l < 2; l++) {
-                const T sc = Rel<S>::value ? T(wgt(i) * D.rho0[l]) : T(1);
-                fo[l][i] = ld_dev<S, T>(own + (l * Q + i) * g.nx, sc);
+                dv[l][m] = row[off + l * Q * g.nx];
+                fv[l][m] = row[ownoff + l * Q * g.nx];
+                rn[l][m] = rho_n[l * S3 + nb];
             }
-        }
-        const double rA = rho_n[b], rB = rho_n[S3 + b];
-        if (links) {
-            // rigid velocity at the link midpoint p + c_i/2: c_i . u_b = c_i . (U + W x d)
-            // with d = p - X, since c_i . (W x c_i) = 0; the torque of the summed
-            // link momentum P about X is d x P for the same reason
-            const double dd[3] = {sepd(p[0] - X[0], g.nx, g.wx), sepd(p[1] - X[1], g.ny, g.wy),
-                                  sepd(p[2] - X[2], g.nz, g.wz)};
-            const double V[3] = {st.U[0] + st.W[1] * dd[2] - st.W[2] * dd[1],
-                                 st.U[1] + st.W[2] * dd[0] - st.W[0] * dd[2],
-                                 st.U[2] + st.W[0] * dd[1] - st.W[1] * dd[0]};
-            const double rl[2] = {rA, rB};
-            double P[3] = {0.0, 0.0, 0.0};
+            pm[m] = pmask[nb];
+        });
+        // rigid velocity at the link midpoint p + c_i/2: c_i . u_b = c_i . (U + W x d)
+        // with d = p - X, since c_i . (W x c_i) = 0; the torque of the summed
+        // link momentum P about X is d x P for the same reason
+        const double V[3] = {U[0] + W[1] * dd[2] - W[2] * dd[1], U[1] + W[2] * dd[0] - W[0] * dd[2],
+                             U[2] + W[0] * dd[1] - W[1] * dd[0]};
+        T v[2][QM];                   // population opp(i) of step n + 1
+        double mx[3][QM], mf[2][QM];  // momentum along c_i, mass flux
+        for_quad_dirs([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            const QDir d = quad_dir<m>(q);
+            const double w = quad_w<m>(q);
+            const bool sn = ok[m] && (pm[m] & MASK_SOLID);
+            double amp = 0.0;
+            mf[0][m] = mf[1][m] = 0.0;
 #pragma unroll
-            for (int i = 1; i < Q; i++) {
-                if (!((links >> i) & 1u)) continue;
-                const double cu = cx(i) * V[0] + cy(i) * V[1] + cz(i) * V[2];
-                double mom = 0.0;
+            for (int l = 0; l < 2; l++)
+                v[l][m] = ld_dev<S, T>(&dv[l][m], Rel<S>::value ? T(w) * T(rho0[l]) : T(1));
+            if (sn && !solid) {  // link
+                const double cu = d.c[0] * V[0] + d.c[1] * V[1] + d.c[2] * V[2];
+                S *to = buf + own + pull_off(p[0], against(d), g);
 #pragma unroll
                 for (int l = 0; l < 2; l++) {
-                    const double wr = wgt(i) * D.rho0[l];
-                    const double fs = wr + (double)fo[l][i];
-                    const double corr = 6.0 * wgt(i) * rl[l] * cu;
-                    mom += 2.0 * fs - corr;
-                    acc[6 + l] -= corr;
-                    d[l][opp(i)] = store_round<S, T>(fs - corr - wr, T(1.0 / wr), T(wgt(i)) * pc.scale[l], sv[l][i]);
+                    const double wr = w * rho0[l];
+                    const double fs = wr + (double)ld_dev<S, T>(&fv[l][m], Rel<S>::value ? T(wr) : T(1));
+                    const double corr = 6.0 * w * rl[l] * cu;
+                    amp += 2.0 * fs - corr;
+                    mf[l][m] = -corr;
+                    S sv;
+                    v[l][m] = store_round<S, T>(fs - corr - wr, Rel<S>::value ? T(1.0 / wr) : T(1),
+                                                Rel<S>::value ? T(w) * T(rho0[l]) : T(1), sv);
+                    to[l * Q * g.nx] = sv;
                 }
-                if (cx(i)) P[0] += cx(i) > 0 ? mom : -mom;
-                if (cy(i)) P[1] += cy(i) > 0 ? mom : -mom;
-                if (cz(i)) P[2] += cz(i) > 0 ? mom : -mom;
-                acc[14] += 1.0;
+                nlinks++;
             }
-            acc[0] += P[0]; acc[1] += P[1]; acc[2] += P[2];
-            acc[3] += dd[1] * P[2] - dd[2] * P[1];
-            acc[4] += dd[2] * P[0] - dd[0] * P[2];
-            acc[5] += dd[0] * P[1] - dd[1] * P[0];
+            if (solid && ok[m] && !sn) {
+                // reaction of the wetting layer: the Shan-Chen force on the fluid
+                // neighbour x = s + c is -sw c (sw = -G w rho_l(x) rho~_l'(s)); its torque
+                // about X is d_s x (-sw c)
+                amp = D.G * w * (rn[0][m] * (vw[1] + dlt[1]) + rn[1][m] * (vw[0] + dlt[0]));
+            }
+#pragma unroll
+            for (int x = 0; x < 3; x++) mx[x][m] = amp * d.c[x];
+        });
+#pragma unroll
+        for (int x = 0; x < 3; x++) vec[x] = chain_sum(mx[x]);
+        mass[0] = chain_sum(mf[0]);
+        mass[1] = chain_sum(mf[1]);
+        if (!solid) {
+            // densities and momentum of step n+1, the populations taken from the
+            // quad's lanes in the order node_moments adds them
+            double mo[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int l = 0; l < 2; l++) {
+                T rd = T(0), j[3] = {T(0), T(0), T(0)};
+#pragma unroll
+                for (int i = 0; i < Q; i++) {
+                    const int from = opp(i) / QM;  // the lane that holds population i
+                    const T x = v[l][opp(i) % QM];
+                    const T u = from == 0 ? quad_bcast<0>(x) : from == 1 ? quad_bcast<1>(x)
+                              : from == 2 ? quad_bcast<2>(x) : quad_bcast<3>(x);
+                    rd += u;
+                    if (cx(i) > 0) j[0] += u; else if (cx(i) < 0) j[0] -= u;
+                    if (cy(i) > 0) j[1] += u; else if (cy(i) < 0) j[1] -= u;
+                    if (cz(i) > 0) j[2] += u; else if (cz(i) < 0) j[2] -= u;
+                }
+                mo[l] = rho0[l] + (double)rd;
+#pragma unroll
+                for (int x = 0; x < 3; x++) mo[2 + x] += (double)j[x];
+            }
+            raw[q * S3 + b] = q == 0 ? mo[0] : q == 1 ? mo[1] : q == 2 ? mo[2] : mo[3];
+            if (q == 0) raw[4 * S3 + b] = mo[4];
         }
-        // densities and momentum of step n+1 at this node
-        NodeM<T> m;
-        node_moments(d, m);
-        rw[0] = D.rho0[0] + (double)m.rd[0];
-        rw[1] = D.rho0[1] + (double)m.rd[1];
-#pragma unroll
-        for (int q = 0; q < 3; q++) rw[2 + q] = (double)m.j[0][q] + (double)m.j[1][q];
     }
-    if (in && !fluid) {
-        // particle node s: reaction of the wetting layer, i.e. the Shan-Chen
-        // force -G rho_l(x) w_k rho~_l'(s) c on each fluid neighbour x = s + c_k
-        // (link direction c = -c_k), summed here from the particle side
-        const double vA = vrho[b] + st.delta[0], vB = vrho[S3 + b] + st.delta[1];
-        double rn[2][Q];
-        uint32_t fl = 0;
-#pragma unroll
-        for (int k = 1; k < Q; k++) {
-            rn[0][k] = rn[1][k] = 0.0;
-            const int xb = box_nb(bb, k, Sx);
-            if (xb < 0 || !nbr_ok(nb, k) || pnode_nb(nb, k)) continue;
-            fl |= 1u << k;
-            rn[0][k] = rho_n[xb];
-            rn[1][k] = rho_n[S3 + xb];
+    nlinks = quad_sum(nlinks);
+    {
+        // lane q of the quad writes its quarter of the node's 15 values
+        const double tq[3] = {dd[1] * vec[2] - dd[2] * vec[1], dd[2] * vec[0] - dd[0] * vec[2],
+                              dd[0] * vec[1] - dd[1] * vec[0]};
+        double *c = red + (t >> 2);
+        if (q < 3) {
+            const double f = q == 0 ? vec[0] : q == 1 ? vec[1] : vec[2];
+            const double m = near ? (q == 0 ? tq[0] : q == 1 ? tq[1] : tq[2]) : 0.0;
+            c[q * 64] = solid ? 0.0 : f;
+            c[(3 + q) * 64] = solid ? 0.0 : m;
+            c[(8 + q) * 64] = solid ? f : 0.0;
+            c[(11 + q) * 64] = solid ? m : 0.0;
+        } else {
+            c[6 * 64] = mass[0];
+            c[7 * 64] = mass[1];
+            c[14 * 64] = (double)nlinks;
         }
-        // force on the fluid neighbour x = s + c_k is -sw c_k; its torque about X
-        // is (d_s + c_k/2) x (-sw c_k) = d_s x (-sw c_k), d_s = s - X
-        double Fw[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-        for (int k = 1; k < Q; k++) {
-            if (!((fl >> k) & 1u)) continue;
-            const double sw = -D.G * wgt(k) * (rn[0][k] * vB + rn[1][k] * vA);
-            if (cx(k)) Fw[0] += cx(k) > 0 ? -sw : sw;
-            if (cy(k)) Fw[1] += cy(k) > 0 ? -sw : sw;
-            if (cz(k)) Fw[2] += cz(k) > 0 ? -sw : sw;
-        }
-        const double ds[3] = {sepd(p[0] - X[0], g.nx, g.wx), sepd(p[1] - X[1], g.ny, g.wy),
-                              sepd(p[2] - X[2], g.nz, g.wz)};
-        acc[8] += Fw[0]; acc[9] += Fw[1]; acc[10] += Fw[2];
-        acc[11] += ds[1] * Fw[2] - ds[2] * Fw[1];
-        acc[12] += ds[2] * Fw[0] - ds[0] * Fw[2];
-        acc[13] += ds[0] * Fw[1] - ds[1] * Fw[0];
     }
-    if (fluid) {
-        // stores: bounced values into the slots p pulls from at p + c_i (a
-        // ghost when the link crosses a periodic face), then the node's raw
-#pragma unroll
-        for (int i = 1; i < Q; i++) {
-            if (!((links >> i) & 1u)) continue;
-            S *tgt = buf + pull_slot(p[0], p[1], p[2], 0, opp(i), g);
-#pragma unroll
-            for (int l = 0; l < 2; l++) tgt[l * Q * g.nx] = sv[l][i];
-        }
-#pragma unroll
-        for (int k = 0; k < RAW; k++) raw[k * S3 + b] = rw[k];
-    }
-    block_sum<B, 15>(acc, red);
-    if (t == 0) {
-        double *pp = a.part1 + D.part3_off + (int64_t)local * PART;
-        for (int k = 0; k < 15; k++) pp[k] = acc[k];
-    }
+    __syncthreads();
+    const double s = row_sum64(red + (t < 240 ? t >> 4 : 0) * 64, t & 15);
+    if (t < 240 && (t & 15) == 0) a.part1[D.part3_off + (int64_t)local * PART + (t >> 4)] = s;
 }
 
 // ============================================================ k_particle
-// One thread per node of the box of X^{n+1}.  Every wave reduces the link
-// sums (fixed order) and advances the sphere: leap-frog Newton-Euler under
+// Four lanes per node of the box of X^{n+1}.  Every workgroup sums the link
+// partials (fixed order) and advances the sphere: leap-frog Newton-Euler under
 // F = links - wetting reaction + F_ext + pending event momentum.  Each node
-// then takes its flags at X^{n+1} (the FP64 predicate, evaluated here for
-// both positions), and
+// then takes its flag at X^{n+1} (the FP64 predicate; the flags at X^n are the
+// ones the last step left), and
 //  * covered (fluid at X^n, particle at X^{n+1}): adds its momentum and
 //    mass to the event sums;
 //  * uncovered (particle at X^n, fluid at X^{n+1}): gets f_eq(rho_bar, u_b)
@@ -1014,411 +1119,505 @@ __global__ __launch_bounds__(B) void k_links(LinkArgs a) {
 //  * particle node at X^{n+1}: gets the wetting-layer density, mean of its
 //    fluid neighbours +/- Delta rho (the mass correction delta is added
 //    where it is read).
-// Each workgroup leaves its event sums as a partial.  They are combined, with
-// the global mass correction and the new state of step n+1, either by the
-// last workgroup to finish (one device-scope fence and atomic per workgroup)
-// or, for large grids, by the separate k_finish launch (finish_apart): each
-// such fence writes back the XCD's L2, which costs more than a launch once
-// many workgroups share an XCD.
-// Leap-frog Newton-Euler step of one sphere from the link sums of step n
-// (momentum exchange minus wetting-layer reaction, plus F_ext and the
-// pending event momentum), and the bounding-box origin of X^{n+1}.  Every
-// caller evaluates it on the same inputs, so all agree bitwise.
+// Each workgroup leaves its event sums as a partial.  The last one to finish
+// (per fluid) combines them, with the global mass correction and the new state
+// of step n+1.  The partials go out as device-scope stores and come back as
+// device-scope loads, each workgroup waiting for its own before it counts
+// itself: a release fence instead writes back the L2 of its XCD (2-3 us, and
+// with thousands of workgroups more than a separate launch).
+
+// Motion of step n+1 of one sphere, in LDS.
 struct Motion {
     double F[3], Tq[3], Un[3], Wn[3], Xn[3];
     int org[3];
 };
 
-__device__ __forceinline__ void newton_euler(const RepDesc &D, const RepState *st, const Geo &g,
-                                             const double (&sum)[15], Motion &m) {
-    const int n3[3] = {g.nx, g.ny, g.nz};
-    const bool w3[3] = {g.wx, g.wy, g.wz};
-    for (int q = 0; q < 3; q++) {
-        m.F[q] = sum[q] - sum[8 + q] + D.Fext[q] + st->Pev[q];
-        m.Tq[q] = sum[3 + q] - sum[11 + q] + st->Lev[q];
-        m.Un[q] = D.fixed_velocity ? st->U[q] : st->U[q] + m.F[q] / D.mp;
-        m.Wn[q] = D.fixed_velocity ? st->W[q] : st->W[q] + m.Tq[q] / D.Ip;
-    }
-    for (int q = 0; q < 3; q++) {
-        m.Xn[q] = st->X[q] + m.Un[q];
-        if (!w3[q]) {
-            if (m.Xn[q] >= n3[q]) m.Xn[q] -= n3[q];
-            else if (m.Xn[q] < 0.0) m.Xn[q] += n3[q];
+// Scratch of a box workgroup: link sums, motion, event totals.
+struct BoxShared {
+    double grp[16][16];
+    double sum[16];
+    double tot[20];
+    uint32_t evw[64];      // workgroups with events, a window of 2048
+    double cnt[K3_THREADS / 64];
+    Motion mo;
+    int32_t org[MAX_GROUP][3];
+    int last;
+};
+
+// Link sums of one sphere (15 values) into sh.sum, the order of sum_partials:
+// column l = 0 .. 63 adds partials l, l + 64, ..., then the balanced tree over
+// the columns (thread t: value t % 16, columns 4 (t / 16) .. + 3).  Ends with a
+// barrier.
+__device__ __forceinline__ void link_sums(const double *part1, int count, BoxShared &sh, int t) {
+    const int k = t & 15, gq = t >> 4;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    if (k < 15) {
+        const double *p = part1 + (int64_t)(4 * gq) * PART + k;
+        for (int w = 4 * gq; w < count; w += 192, p += 192 * PART) {
+            double c[3][4];
+#pragma unroll
+            for (int m = 0; m < 3; m++)
+#pragma unroll
+                for (int j = 0; j < 4; j++) c[m][j] = w + 64 * m + j < count ? p[(64 * m + j) * PART] : 0.0;
+#pragma unroll
+            for (int m = 0; m < 3; m++)
+#pragma unroll
+                for (int j = 0; j < 4; j++) s[j] += c[m][j];
         }
-        m.org[q] = (int)floor(m.Xn[q] - D.radius) - 2;  // box of X^{n+1}
     }
+    __syncthreads();  // earlier readers of sh.grp are done
+    sh.grp[gq][k] = (s[0] + s[1]) + (s[2] + s[3]);
+    __syncthreads();
+    if (t < 15) {
+        double v[16];
+#pragma unroll
+        for (int j = 0; j < 16; j++) v[j] = sh.grp[j][t];
+#pragma unroll
+        for (int h = 1; h < 16; h *= 2)
+#pragma unroll
+            for (int j = 0; j < 16; j += 2 * h) v[j] += v[j + h];
+        sh.sum[t] = v[0];
+    }
+    __syncthreads();
+}
+
+// Leap-frog Newton-Euler step of one sphere from the link sums of step n
+// (momentum exchange minus wetting-layer reaction, plus F_ext and the
+// pending event momentum), and the bounding-box origin of X^{n+1}: one thread
+// per axis.  Every caller evaluates it on the same inputs, so all agree
+// bitwise.  Ends with a barrier.
+struct Axis {  // what it reads of one axis; loaded before the link sums
+    double X, U, W, Fext, Pev, Lev, mp, Ip;
+};
+__device__ __forceinline__ Axis axis_of(const RepDesc &D, const RepState *st, int t) {
+    const int x = t < 3 ? t : 0;
+    return {st->X[x], st->U[x], st->W[x], D.Fext[x], st->Pev[x], st->Lev[x], D.mp, D.Ip};
+}
+__device__ __forceinline__ void newton_euler(const RepDesc &D, const Axis &ax, const Geo &g, BoxShared &sh, int t) {
+    if (t < 3) {
+        const double (&sum)[16] = sh.sum;
+        const int n = t == 0 ? g.nx : t == 1 ? g.ny : g.nz;
+        const bool wall = t == 0 ? g.wx : t == 1 ? g.wy : g.wz;
+        const double U = ax.U, W = ax.W;
+        const double F = sum[t] - sum[8 + t] + ax.Fext + ax.Pev;
+        const double Tq = sum[3 + t] - sum[11 + t] + ax.Lev;
+        const double Un = D.fixed_velocity ? U : U + F / ax.mp;
+        double Xn = ax.X + Un;
+        if (!wall) {
+            if (Xn >= n) Xn -= n;
+            else if (Xn < 0.0) Xn += n;
+        }
+        sh.mo.F[t] = F;
+        sh.mo.Tq[t] = Tq;
+        sh.mo.Un[t] = Un;
+        sh.mo.Wn[t] = D.fixed_velocity ? W : W + Tq / ax.Ip;
+        sh.mo.Xn[t] = Xn;
+        sh.mo.org[t] = (int)floor(Xn - D.radius) - 2;  // box of X^{n+1}
+    }
+    __syncthreads();
+}
+
+// device-scope access to the event partials (see above)
+__device__ __forceinline__ void put_dev(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double get_dev(const double *p) {
+    return __hip_atomic_load(const_cast<double *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Event totals of one sphere into sh.tot, the order of sum_partials.  Slot 9
+// (particle nodes) and slot 20 (events in this workgroup) are in every partial;
+// the other slots are read from the workgroups that had events and are zero
+// elsewhere (adding zero changes nothing).  col: 20 x 64 columns.  Ends with a
+// barrier.
+__device__ __forceinline__ void event_totals(const double *part3, int count, BoxShared &sh, double *col, int t) {
+    double cnt = 0.0;
+    bool any = false;
+    __syncthreads();
+    for (int w0 = 0; w0 < count; w0 += 2048) {
+        if (t < 64) sh.evw[t] = 0u;
+        __syncthreads();
+        bool mine = false;
+        for (int w = w0 + t; w < min(count, w0 + 2048); w += K3_THREADS) {
+            cnt += get_dev(part3 + (int64_t)w * PART + 9);
+            if (get_dev(part3 + (int64_t)w * PART + 20) != 0.0) {
+                atomicOr(&sh.evw[(w - w0) >> 5], 1u << ((w - w0) & 31));
+                mine = true;
+            }
+        }
+        if (!__syncthreads_or(mine)) continue;
+        if (!any)
+            for (int e = t; e < 20 * 64; e += K3_THREADS) col[e] = 0.0;
+        any = true;
+        __syncthreads();
+        if (t < 64)  // words with a bit set, in ascending order
+            for (uint64_t words = __ballot(sh.evw[t] != 0u); words; words &= words - 1) {
+                const int k = __builtin_ctzll(words);
+                for (uint32_t e = sh.evw[k]; e; e &= e - 1) {
+                    const int w = w0 + 32 * k + __builtin_ctz(e);
+                    if (t < 20 && t != 9) col[t * 64 + (w & 63)] += get_dev(part3 + (int64_t)w * PART + t);
+                }
+            }
+        __syncthreads();
+    }
+    // whole numbers: exact in any order
+    double c[1] = {cnt};
+    wave_sum<1>(c);
+    if ((t & 63) == 0) sh.cnt[t >> 6] = c[0];
+    if (any) {
+        const double a = row_sum64(col + (t >> 4) * 64, t & 15);
+        const double b = row_sum64(col + (16 + ((t >> 4) & 3)) * 64, t & 15);
+        if ((t & 15) == 0) sh.tot[t >> 4] = a;
+        if ((t & 15) == 0 && t < 64) sh.tot[16 + (t >> 4)] = b;
+    } else if (t < 20) {
+        sh.tot[t] = 0.0;
+    }
+    __syncthreads();
+    if (t == 0) sh.tot[9] = (sh.cnt[0] + sh.cnt[1]) + (sh.cnt[2] + sh.cnt[3]);
+    __syncthreads();
+}
+
+// slot of step n in a U-series ring
+__device__ __forceinline__ int64_t ring_slot(int64_t n, int cap) {
+    return n < ((int64_t)1 << 31) ? (int64_t)((uint32_t)n % (uint32_t)cap) : n % cap;
 }
 
 // A replica without a sphere: record U = 0 and advance the step counter.
 __device__ __forceinline__ void advance_empty(const ParticleArgs &a, const RepDesc &D, RepState *st) {
     const int64_t n = st->step;
-    double *s = a.series + D.series_off + 3 * (n % D.series_cap);
+    double *s = a.series + D.series_off + 3 * ring_slot(n, D.series_cap);
     s[0] = s[1] = s[2] = 0.0;
     st->delta[0] = st->delta[1] = 0.0;
     st->step = n + 1;
 }
 
-// Motion of step n+1 of one sphere (one thread): position, velocities,
-// forces, bounding-box origin, pending event momentum, the U series entry and
-// the event counters.  Returns whether the sphere went unstable (|U| >= 1/2,
-// a non-finite force) or reached a wall.
-__device__ __forceinline__ bool publish_motion(const ParticleArgs &a, const RepDesc &D, RepState *st,
-                                               const Geo &g, const double (&sum)[15], const Motion &mo,
-                                               const double (&tot)[20]) {
-    const int n3[3] = {g.nx, g.ny, g.nz};
-    const bool w3[3] = {g.wx, g.wy, g.wz};
-    const double Xold[3] = {st->X[0], st->X[1], st->X[2]};
-    const double *utot = tot + 10;
+// Motion of step n+1 of one sphere (threads 0 .. 2, one per axis): position,
+// velocities, forces, bounding-box origin, pending event momentum, the U series
+// entry and (thread 0) the event counters.  Returns in each of these threads
+// whether the sphere went unstable (|U| >= 1/2, a non-finite force) or reached a
+// wall on its axis.
+__device__ __forceinline__ bool publish_motion(const ParticleArgs &a, const RepDesc &D, RepState *st, const Geo &g,
+                                               const BoxShared &sh, int t) {
+    if (t >= 3) return false;
+    const Motion &mo = sh.mo;
     const int64_t n = st->step;
-    double *s = a.series + D.series_off + 3 * (n % D.series_cap);
-    bool bad = false;
-    for (int q = 0; q < 3; q++) {
-        st->Xp[q] = Xold[q];
-        st->X[q] = mo.Xn[q];
-        st->U[q] = mo.Un[q];
-        st->W[q] = mo.Wn[q];
-        st->F[q] = mo.F[q];
-        st->T[q] = mo.Tq[q];
-        st->Pev[q] = tot[q] - utot[q];
-        st->Lev[q] = tot[3 + q] - utot[3 + q];
-        st->org[q] = mo.org[q];
-        s[q] = mo.Un[q];
-        if (q == 2) st->uz_sum += mo.Un[2];
-        if (!(fabs(mo.Un[q]) < 0.5) || !isfinite(mo.F[q])) bad = true;
-        if (w3[q] && (mo.Xn[q] - D.radius < -0.5 || mo.Xn[q] + D.radius > n3[q] - 0.5)) bad = true;
+    const int nn = t == 0 ? g.nx : t == 1 ? g.ny : g.nz;
+    const bool wall = t == 0 ? g.wx : t == 1 ? g.wy : g.wz;
+    const double Xold = st->X[t];
+    st->Xp[t] = Xold;
+    st->X[t] = mo.Xn[t];
+    st->U[t] = mo.Un[t];
+    st->W[t] = mo.Wn[t];
+    st->F[t] = mo.F[t];
+    st->T[t] = mo.Tq[t];
+    st->Pev[t] = sh.tot[t] - sh.tot[10 + t];
+    st->Lev[t] = sh.tot[3 + t] - sh.tot[13 + t];
+    st->org[t] = mo.org[t];
+    a.series[D.series_off + 3 * ring_slot(n, D.series_cap) + t] = mo.Un[t];
+    if (t == 2) st->uz_sum += mo.Un[2];
+    if (t == 0) {
+        st->n_cov += (int64_t)sh.tot[8];
+        st->n_unc += (int64_t)sh.tot[18];
+        st->n_links = (int64_t)sh.sum[14];
     }
-    st->n_cov += (int64_t)tot[8];
-    st->n_unc += (int64_t)utot[8];
-    st->n_links = (int64_t)sum[14];
-    return bad;
+    return !(fabs(mo.Un[t]) < 0.5) || !isfinite(mo.F[t]) ||
+           (wall && (mo.Xn[t] - D.radius < -0.5 || mo.Xn[t] + D.radius > nn - 0.5));
 }
 
 // Publish step n+1 of one replica with a single sphere from the link sums,
-// the motion and the event totals (one thread): global mass correction
+// the motion and the event totals (one workgroup): global mass correction
 // delta_l = -(bounce-back flux - covered + uncovered mass)_l / |Phi^{n+1}|,
 // then the sphere's motion, the step counter and the stability flag.
-__device__ __forceinline__ void publish_step(const ParticleArgs &a, const RepDesc &D, RepState *st,
-                                             const Geo &g, const double (&sum)[15], const Motion &mo,
-                                             const double (&tot)[20]) {
-    const double *utot = tot + 10;
-    const double nf = (double)D.N - tot[9];
-    for (int l = 0; l < 2; l++) st->delta[l] = -(sum[6 + l] - tot[6 + l] + utot[6 + l]) / nf;
-    const bool bad = publish_motion(a, D, st, g, sum, mo, tot);
-    st->n_fluid = nf;
-    if (bad) st->flags |= FLAG_UNSTABLE;
-    st->step = st->step + 1;
+__device__ __forceinline__ void publish_step(const ParticleArgs &a, const RepDesc &D, RepState *st, const Geo &g,
+                                             const BoxShared &sh, int t) {
+    if (t >= 64) return;
+    const double nf = (double)D.N - sh.tot[9];
+    const bool bad = publish_motion(a, D, st, g, sh, t);
+    const bool any = __any(bad);
+    if (t < 2) st->delta[t] = -(sh.sum[6 + t] - sh.tot[6 + t] + sh.tot[16 + t]) / nf;
+    if (t == 0) {
+        st->n_fluid = nf;
+        if (any) st->flags |= FLAG_UNSTABLE;
+        st->step = st->step + 1;
+        st->k3_done = 0;
+    }
 }
 
-// Publish step n+1 of a group of spheres in one fluid (one wave; lane 0
-// writes).  The mass correction is global: the bounce-back, covered and
-// uncovered fluxes and the particle nodes of every sphere are summed before
-// delta_l and |Phi^{n+1}| are formed.  Each sphere then takes its own
-// Newton-Euler step, and every entry of the group receives the shared fields
-// (delta, fluid nodes, step, flags).  Two boxes that now share a node set
-// FLAG_CONTACT on the group.
-__device__ __forceinline__ void publish_group(const ParticleArgs &a, int prim, const Geo &g) {
+// Publish step n+1 of a group of spheres in one fluid (one workgroup).  The
+// mass correction is global: the bounce-back, covered and uncovered fluxes and
+// the particle nodes of every sphere are summed before delta_l and |Phi^{n+1}|
+// are formed.  Each sphere then takes its own Newton-Euler step, and every
+// entry of the group receives the shared fields (delta, fluid nodes, step,
+// flags).  Two boxes that now share a node set FLAG_CONTACT on the group.
+__device__ __forceinline__ void publish_group(const ParticleArgs &a, int prim, const Geo &g, BoxShared &sh,
+                                              double *col, int t) {
     const RepDesc *P = a.desc + prim;
     const int K = P->n_sph;
     double dm[2] = {0.0, 0.0}, nsol = 0.0;
-    for (int e = prim; e < prim + K; e++) {
-        const RepDesc *De = a.desc + e;
-        double sum[15], tot[20];
-        sum_partials<15>(a.part1 + De->part3_off, De->k3_count, 0, sum);
-        sum_partials<20>(a.part3 + De->part3_off, De->k3_count, 0, tot);
-        for (int l = 0; l < 2; l++) dm[l] += sum[6 + l] - tot[6 + l] + tot[16 + l];
-        nsol += tot[9];
-    }
-    const double nf = (double)P->N - nsol;
-    const double delta[2] = {-dm[0] / nf, -dm[1] / nf};
     uint32_t flags = 0u;
-    for (int e = prim; e < prim + K; e++) flags |= a.state[e].flags;
-    const bool lead = (threadIdx.x & 63) == 0;
     for (int e = prim; e < prim + K; e++) {
         const RepDesc &De = a.desc[e];
         RepState *se = a.state + e;
-        double sum[15], tot[20];
-        sum_partials<15>(a.part1 + De.part3_off, De.k3_count, 0, sum);
-        sum_partials<20>(a.part3 + De.part3_off, De.k3_count, 0, tot);
-        Motion mo;
-        newton_euler(De, se, g, sum, mo);
-        if (lead && publish_motion(a, De, se, g, sum, mo, tot)) flags |= FLAG_UNSTABLE;
+        flags |= se->flags;
+        const Axis ax = axis_of(De, se, t);
+        link_sums(a.part1 + De.part3_off, De.k3_count, sh, t);
+        event_totals(a.part3 + De.part3_off, De.k3_count, sh, col, t);
+        newton_euler(De, ax, g, sh, t);
+        for (int l = 0; l < 2; l++) dm[l] += sh.sum[6 + l] - sh.tot[6 + l] + sh.tot[16 + l];
+        nsol += sh.tot[9];
+        if (t < 64) {
+            const bool bad = publish_motion(a, De, se, g, sh, t);
+            if (__any(bad)) flags |= FLAG_UNSTABLE;
+        }
+        if (t < 3) sh.org[e - prim][t] = sh.mo.org[t];
     }
-    if (!lead) return;
+    __syncthreads();
+    if (t != 0) return;
+    const double nf = (double)P->N - nsol;
     const int32_t n3[3] = {g.nx, g.ny, g.nz};
-    for (int e = prim; e < prim + K; e++)
-        for (int f = e + 1; f < prim + K; f++)
-            if (boxes_overlap(a.state[e].org, a.desc[e].S, a.state[f].org, a.desc[f].S, n3, P->walls))
+    for (int e = 0; e < K; e++)
+        for (int f = e + 1; f < K; f++)
+            if (boxes_overlap(sh.org[e], a.desc[prim + e].S, sh.org[f], a.desc[prim + f].S, n3, P->walls))
                 flags |= FLAG_CONTACT;
     const int64_t step = a.state[prim].step + 1;
     for (int e = prim; e < prim + K; e++) {
         RepState *se = a.state + e;
-        se->delta[0] = delta[0];
-        se->delta[1] = delta[1];
+        se->delta[0] = -dm[0] / nf;
+        se->delta[1] = -dm[1] / nf;
         se->n_fluid = nf;
         se->flags = flags;
         se->step = step;
     }
+    a.state[prim].k3_done = 0;
 }
 
-template <typename S, typename T, int B, bool APART>
-__global__ __launch_bounds__(B) void k_particle(ParticleArgs a) {
-    static_assert(B == 64, "the uncovered-density jobs are shared within one wave");
-    __shared__ double red[(B / 64) * 20];
-    __shared__ int last;
-    __shared__ int job_desc[64];   // owner lane | direction << 8 (0: the owner itself)
-    __shared__ int job_pos[64][3];
-    __shared__ Rho2 job_res[64];
-    const int wg = blockIdx.x;
-    const int r = find_rep(a.k3_begin, a.nrep, wg);
-    const RepDesc *__restrict__ dp = a.desc + r;  // read-only in this kernel
-    const RepDesc &D = *dp;
+template <typename S, typename T>
+__global__ __launch_bounds__(K3_THREADS) void k_particle(ParticleArgs a) {
+    __shared__ BoxShared sh;
+    __shared__ double ev[20 * K3_NODES];
+    const int r = find_rep(a.k3_begin, a.nrep, blockIdx.x);
+    const RepDesc &D = a.desc[r];
     RepState *st = a.state + r;
-    const Geo g = geo_of(D);
-    const int t = threadIdx.x;
-    const int local = wg - D.k3_begin;
+    const int t = threadIdx.x, q = t & 3;
+    const int local = blockIdx.x - D.k3_begin;
     if (!D.has_particle) {
-        if (!APART && t == 0) advance_empty(a, D, st);
+        if (t == 0) advance_empty(a, D, st);
         return;
     }
-    double X[3];
-    int32_t orgo[3];
-    for (int q = 0; q < 3; q++) {
-        X[q] = st->X[q]; orgo[q] = st->org[q];
-    }
+    const Geo g = geo_of(D);
+    const int32_t orgo[3] = {st->org[0], st->org[1], st->org[2]};
+    const Axis ax = axis_of(D, st, t);
     // 1. link momentum exchange and wetting-layer reaction of step n
-    double sum[15];
-    sum_partials<15>(a.part1 + D.part3_off, D.k3_count, 0, sum);
+    link_sums(a.part1 + D.part3_off, D.k3_count, sh, t);
     // 2. Newton-Euler, leap-frog
-    Motion mo;
-    newton_euler(D, st, g, sum, mo);
-    const double(&Un)[3] = mo.Un;
-    const double(&Wn)[3] = mo.Wn;
-    const double(&Xn)[3] = mo.Xn;
-    const int(&org)[3] = mo.org;
+    newton_euler(D, ax, g, sh, t);
+    const double Xn[3] = {sh.mo.Xn[0], sh.mo.Xn[1], sh.mo.Xn[2]};
+    const int org[3] = {sh.mo.org[0], sh.mo.org[1], sh.mo.org[2]};
     const int Sx = D.S, S3 = Sx * Sx * Sx;
     const double *raw = a.raw + D.bbox_off * RAW;
     double *vrho = a.vrho + D.bbox_off * 2;
-    uint32_t *pmask = a.pmask + D.bbox_off;
+    const uint32_t *pold = a.pmask_old + D.bbox_off;
+    uint32_t *pnew = a.pmask + D.bbox_off;
     S *buf = reinterpret_cast<S *>(a.buf) + D.pop_off;
 
     // 3. events and wetting layer
-    double ev[20];
-#pragma unroll
-    for (int k = 0; k < 20; k++) ev[k] = 0.0;
-    const int b = local * B + t;
-    int bb[3] = {0, 0, 0}, p[3] = {0, 0, 0};
-    const bool in = b < S3 && bbox_pos(b, org, Sx, g, bb, p);
-    Nbr no, nn;
-    nbr_of(p, X, D.R2, g, no);
-    nbr_of(p, Xn, D.R2, g, nn);
-    const bool fo = in && !pnode_nb(no, 0);
-    const bool fn = in && !pnode_nb(nn, 0);
+    const int b = local * K3_NODES + (t >> 2);
+    int bb[3], p[3];
+    const bool in = box_node(b, org, Sx, g, bb, p);
+    // box coordinates in the box of X^n
     int bo[3];
-    const bool inbox = box_coords(p, orgo, Sx, g, bo);
-    // Loads and arithmetic first, every store last (loads and stores share
-    // one wait counter here).
-    //
-    // A particle node at X^{n+1} (covered ones included) takes the wetting
-    // layer: the mean density of its neighbours fluid at X^{n+1}.  A neighbour
-    // uncovered at this step carries the mean density of its own kept
-    // neighbours (its f_eq density), and an uncovered node needs that mean for
-    // itself.  Those means are jobs shared out over the wave's lanes, 64 per
-    // round, so that a lane with several of them does not run them one after
-    // another while the rest of the wave waits.
-    const bool pn = in && !fn;         // particle node at X^{n+1}
-    const bool unc = in && !fo && fn;  // uncovered at this step
-    int idx[Q];
-    uint32_t kept = 0, fresh = 0;  // fluid at X^{n+1}; of those, uncovered now
-    if (pn) {
+    const int n3[3] = {g.nx, g.ny, g.nz};
+    const bool w3[3] = {g.wx, g.wy, g.wz};
 #pragma unroll
-        for (int i = 1; i < Q; i++) {
-            idx[i] = -1;
-            if (!nbr_ok(nn, i) || pnode_nb(nn, i)) continue;
-            if (pnode_nb(no, i)) {
-                fresh |= 1u << i;
-            } else {
-                idx[i] = inbox ? box_nb(bo, i, Sx) : -1;
-                if (idx[i] < 0) continue;
+    for (int x = 0; x < 3; x++) {
+        int s = org[x] - orgo[x];
+        if (!w3[x]) s = 2 * s > n3[x] ? s - n3[x] : (2 * s < -n3[x] ? s + n3[x] : s);
+        bo[x] = bb[x] + s;
+    }
+    const int zero[3] = {0, 0, 0};
+    const int ob = box_at(bo, zero, Sx);
+    const bool so = in && ob >= 0 && (pold[ob < 0 ? 0 : ob] & MASK_SOLID);  // particle node at X^n
+    const bool sn = in && pnode(p[0], p[1], p[2], Xn, D.R2, g);             // at X^{n+1}
+    const bool unc = so && !sn, cov = in && !so && sn;
+
+    // neighbours of lattice node c (old-box coordinates cb) along this lane's
+    // directions that are fluid at X^{n+1}: those fluid at X^n too (kept) and
+    // those uncovered now (fresh), as bits m; their post-streaming densities are
+    // loaded beside the flags (meaningful for kept ones only)
+    auto flags_of = [&](const int (&c)[3], const int (&cb)[3], uint32_t &kept, uint32_t &fresh, double (&v)[2][QM]) {
+        kept = fresh = 0u;
+        uint32_t pm[QM];
+        int idx[QM];
+        for_quad_dirs([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            const QDir d = quad_dir<m>(q);
+            idx[m] = d.valid ? box_at(cb, d.c, Sx) : -1;
+            const int at = idx[m] < 0 ? 0 : idx[m];
+            pm[m] = pold[at];
+            v[0][m] = raw[at];
+            v[1][m] = raw[S3 + at];
+        });
+        for_quad_dirs([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            const QDir d = quad_dir<m>(q);
+            int np[3];
+            if (!d.valid || !step_to(c, d.c, g, np) || pnode(np[0], np[1], np[2], Xn, D.R2, g)) return;
+            if (idx[m] < 0) return;
+            if (pm[m] & MASK_SOLID) fresh |= 1u << m;
+            else kept |= 1u << m;
+        });
+    };
+    // sums of the kept neighbours' densities, in the four lanes of the quad
+    auto sum_kept = [&](uint32_t kept, const double (&v)[2][QM], double (&s)[2]) {
+#pragma unroll
+        for (int l = 0; l < 2; l++) {
+            double x[QM];
+#pragma unroll
+            for (int m = 0; m < QM; m++) x[m] = (kept >> m) & 1u ? v[l][m] : 0.0;
+            s[l] = chain_sum(x);
+        }
+    };
+    // their mean (rho0 when there is none): the density of an uncovered node
+    auto mean_kept = [&](uint32_t kept, const double (&v)[2][QM], double (&m2)[2]) {
+        sum_kept(kept, v, m2);
+        const int cnt = quad_sum(__builtin_popcount(kept));
+#pragma unroll
+        for (int l = 0; l < 2; l++) m2[l] = cnt > 0 ? m2[l] / cnt : D.rho0[l];
+    };
+    uint32_t kept = 0, fresh = 0;
+    double v[2][QM];
+    const bool work = sn || unc;  // the same in the four lanes of a quad
+    if (work) flags_of(p, bo, kept, fresh, v);
+    double self[2] = {0.0, 0.0};
+    if (unc) mean_kept(kept, v, self);
+    // Densities of a particle node's fresh neighbours: each is the mean over that
+    // neighbour's own kept neighbours, formed by the whole quad.
+    double fs[2] = {0.0, 0.0};
+    if (sn && quad_or(fresh)) {
+        // (in the order of the directions)
+#pragma unroll 1
+        for (int s = 0; s < 4; s++) {
+            if (!quad_or(q == s ? fresh : 0u)) continue;
+#pragma unroll 1
+            for (int m = 0; m < QM; m++) {
+                // lane s's direction 5 s + m of the quad's node, in every lane of the quad
+                const int i = QM * s + m;
+                const bool has = quad_or(q == s ? (fresh >> m) & 1u : 0u) != 0u;
+                if (!has) continue;
+                const int c[3] = {cx(i), cy(i), cz(i)};
+                int np[3], nb[3];
+                step_to(p, c, g, np);
+#pragma unroll
+                for (int x = 0; x < 3; x++) nb[x] = bo[x] + c[x];
+                uint32_t k2, f2;
+                double v2[2][QM], m2[2];
+                flags_of(np, nb, k2, f2, v2);
+                mean_kept(k2, v2, m2);
+                fs[0] += m2[0];
+                fs[1] += m2[1];
             }
-            kept |= 1u << i;
         }
     }
-    const uint32_t jobs = pn ? fresh : (unc ? 1u : 0u);  // bit i: neighbour i; bit 0: itself
-    double fs[2] = {0.0, 0.0};  // fresh neighbours' densities, summed in direction order
-    Rho2 rself = {0.0, 0.0};    // an uncovered node's own mean
-    {
-        const int cnt = __builtin_popcount(jobs);
-        int incl = cnt;  // inclusive prefix sum of the job counts over the wave
-        for (int d = 1; d < 64; d <<= 1) {
-            const int v = __shfl_up(incl, d);
-            if (t >= d) incl += v;
-        }
-        const int excl = incl - cnt;
-        const int total = __shfl(incl, 63);
-        if (total > 0) {  // uniform over the wave (one wave per workgroup)
-            job_pos[t][0] = p[0];
-            job_pos[t][1] = p[1];
-            job_pos[t][2] = p[2];
-            for (int base = 0; base < total; base += 64) {
-                int m = excl;
-                for (uint32_t w = jobs; w; w &= w - 1, m++)
-                    if (m >= base && m < base + 64) job_desc[m - base] = t | (__builtin_ctz(w) << 8);
-                __syncthreads();
-                if (t < total - base) {
-                    const int d = job_desc[t], owner = d & 255, i = d >> 8;
-                    const int o[3] = {job_pos[owner][0], job_pos[owner][1], job_pos[owner][2]};
-                    int q[3] = {o[0], o[1], o[2]};
-                    if (i > 0) nb_pos(o, i, g, q);
-                    job_res[t] = mean_kept(q[0], q[1], q[2], Pos3{{X[0], X[1], X[2]}}, Pos3{{Xn[0], Xn[1], Xn[2]}},
-                                           D.R2, raw, Org3{{orgo[0], orgo[1], orgo[2]}}, Sx, S3, g,
-                                           D.rho0[0], D.rho0[1]);
+    if (sn) {
+        // wetting layer: mean density of the neighbours fluid at X^{n+1}
+        double s[2];
+        sum_kept(kept, v, s);
+        const double s0 = s[0] + fs[0], s1 = s[1] + fs[1];
+        const int cnt = quad_sum(__builtin_popcount(kept | fresh));
+        if (q == 0) vrho[b] = cnt > 0 ? s0 / cnt + D.drho : 0.0;
+        if (q == 1) vrho[S3 + b] = cnt > 0 ? s1 / cnt - D.drho : 0.0;
+    }
+    if (q == 0 && b < S3) pnew[b] = sn ? MASK_SOLID : 0u;
+    const int nsolid = __syncthreads_count(sn && q == 0);
+    const bool events = __syncthreads_or(unc || (cov && ob >= 0));
+    double *pp = a.part3 + D.part3_off + (int64_t)local * PART;
+    if (events) {
+        if (unc) {  // f_eq of its neighbours' mean density and u_b
+            const double rr[3] = {sepd(p[0] - Xn[0], g.nx, g.wx), sepd(p[1] - Xn[1], g.ny, g.wy),
+                                  sepd(p[2] - Xn[2], g.nz, g.wz)};
+            const double *Un = sh.mo.Un, *Wn = sh.mo.Wn;
+            const double u[3] = {Un[0] + Wn[1] * rr[2] - Wn[2] * rr[1], Un[1] + Wn[2] * rr[0] - Wn[0] * rr[2],
+                                 Un[2] + Wn[0] * rr[1] - Wn[1] * rr[0]};
+            const double uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+            S *row = buf + slot_at(p[0], p[1], p[2], 0, g);
+            for_quad_dirs([&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                const QDir d = quad_dir<m>(q);
+                if (d.i >= Q) return;
+                const double w = quad_w<m>(q);
+                const double cu = d.c[0] * u[0] + d.c[1] * u[1] + d.c[2] * u[2];
+                const double e = 1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * uu;
+                S *to = row + pull_off(p[0], d, g);
+#pragma unroll
+                for (int l = 0; l < 2; l++) {
+                    const double wr = w * D.rho0[l];
+                    st_dev<S, T>(to + l * Q * g.nx, T(w * self[l] * e - wr), Rel<S>::value ? T(1.0 / wr) : T(1));
                 }
-                __syncthreads();
-                m = excl;
-                for (uint32_t w = jobs; w; w &= w - 1, m++) {
-                    if (m < base || m >= base + 64) continue;
-                    const Rho2 rb = job_res[m - base];
-                    if (__builtin_ctz(w) == 0) {
-                        rself = rb;
-                    } else {
-                        fs[0] += rb.a;
-                        fs[1] += rb.b;
-                    }
+            });
+        }
+        if (q == 0) {
+            double o[20];
+#pragma unroll
+            for (int k = 0; k < 20; k++) o[k] = 0.0;
+            if (unc || (cov && ob >= 0)) {
+                const double rr[3] = {sepd(p[0] - Xn[0], g.nx, g.wx), sepd(p[1] - Xn[1], g.ny, g.wy),
+                                      sepd(p[2] - Xn[2], g.nz, g.wz)};
+                double j[3], m2[2];
+                if (cov) {
+                    for (int x = 0; x < 3; x++) j[x] = raw[(2 + x) * S3 + ob];
+                    m2[0] = raw[ob];
+                    m2[1] = raw[S3 + ob];
+                } else {
+                    const double *Un = sh.mo.Un, *Wn = sh.mo.Wn;
+                    const double tot = self[0] + self[1];
+                    j[0] = tot * (Un[0] + Wn[1] * rr[2] - Wn[2] * rr[1]);
+                    j[1] = tot * (Un[1] + Wn[2] * rr[0] - Wn[0] * rr[2]);
+                    j[2] = tot * (Un[2] + Wn[0] * rr[1] - Wn[1] * rr[0]);
+                    m2[0] = self[0];
+                    m2[1] = self[1];
                 }
-                __syncthreads();
-            }
-        }
-    }
-    double vw[2] = {0.0, 0.0};
-    if (pn) {
-        ev[9] += 1.0;
-        double r0[Q], r1[Q];
+                const double e9[9] = {j[0], j[1], j[2], rr[1] * j[2] - rr[2] * j[1], rr[2] * j[0] - rr[0] * j[2],
+                                      rr[0] * j[1] - rr[1] * j[0], m2[0], m2[1], 1.0};
 #pragma unroll
-        for (int i = 1; i < Q; i++) {
-            r0[i] = r1[i] = 0.0;
-            if (((kept & ~fresh) >> i) & 1u) {
-                r0[i] = raw[idx[i]];
-                r1[i] = raw[S3 + idx[i]];
+                for (int k = 0; k < 9; k++) {
+                    o[k] = cov ? e9[k] : 0.0;
+                    o[10 + k] = cov ? 0.0 : e9[k];
+                }
             }
-        }
-        double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-        for (int i = 1; i < Q; i++) {
-            if (!(((kept & ~fresh) >> i) & 1u)) continue;
-            s0 += r0[i];
-            s1 += r1[i];
+            for (int k = 0; k < 20; k++) ev[k * K3_NODES + (t >> 2)] = o[k];
         }
-        s0 += fs[0];
-        s1 += fs[1];
-        const int cnt = __builtin_popcount(kept);
-        vw[0] = cnt > 0 ? s0 / cnt + D.drho : 0.0;
-        vw[1] = cnt > 0 ? s1 / cnt - D.drho : 0.0;
+        __syncthreads();
+        // rows 0 .. 15, then 16 .. 19
+        double s = row_sum64(ev + (t >> 4) * K3_NODES, t & 15);
+        if ((t & 15) == 0 && (t >> 4) != 9) put_dev(pp + (t >> 4), s);
+        s = row_sum64(ev + (16 + ((t >> 4) & 3)) * K3_NODES, t & 15);
+        if (t < 64 && (t & 15) == 0) put_dev(pp + 16 + (t >> 4), s);
     }
-    if (fo && !fn && inbox) {  // covered
-        const int ob = (bo[2] * Sx + bo[1]) * Sx + bo[0];
-        const double rho[2] = {raw[ob], raw[S3 + ob]};
-        const double jt[3] = {raw[2 * S3 + ob], raw[3 * S3 + ob], raw[4 * S3 + ob]};
-        const double rr[3] = {sepd(p[0] - Xn[0], g.nx, g.wx), sepd(p[1] - Xn[1], g.ny, g.wy),
-                              sepd(p[2] - Xn[2], g.nz, g.wz)};
-        ev[0] += jt[0]; ev[1] += jt[1]; ev[2] += jt[2];
-        ev[3] += rr[1] * jt[2] - rr[2] * jt[1];
-        ev[4] += rr[2] * jt[0] - rr[0] * jt[2];
-        ev[5] += rr[0] * jt[1] - rr[1] * jt[0];
-        ev[6] += rho[0];
-        ev[7] += rho[1];
-        ev[8] += 1.0;
-    }
-    if (b < S3) {
-        pmask[b] = (in && !fn) ? MASK_SOLID : 0u;
-        if (in && !fn) {
-            vrho[b] = vw[0];
-            vrho[S3 + b] = vw[1];
-        }
-    }
-    if (unc) {  // uncovered (rare): f_eq of its neighbours' mean density and u_b
-        const double rb[2] = {rself.a, rself.b};
-        const double rr[3] = {sepd(p[0] - Xn[0], g.nx, g.wx), sepd(p[1] - Xn[1], g.ny, g.wy),
-                              sepd(p[2] - Xn[2], g.nz, g.wz)};
-        const double u[3] = {Un[0] + Wn[1] * rr[2] - Wn[2] * rr[1],
-                             Un[1] + Wn[2] * rr[0] - Wn[0] * rr[2],
-                             Un[2] + Wn[0] * rr[1] - Wn[1] * rr[0]};
-        const double uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-        for (int i = 0; i < Q; i++) {
-            const double cu = cx(i) * u[0] + cy(i) * u[1] + cz(i) * u[2];
-            const double e = 1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * uu;
-            S *to = buf + pull_slot(p[0], p[1], p[2], 0, i, g);
-            for (int l = 0; l < 2; l++) {
-                const double wr = wgt(i) * D.rho0[l];
-                const double dev = wgt(i) * rb[l] * e - wr;
-                st_dev<S, T>(to + l * Q * g.nx, T(dev),
-                             Rel<S>::value ? T(1.0 / wr) : T(1));
-            }
-        }
-        const double mom[3] = {(rb[0] + rb[1]) * u[0], (rb[0] + rb[1]) * u[1],
-                               (rb[0] + rb[1]) * u[2]};
-        ev[10] += mom[0]; ev[11] += mom[1]; ev[12] += mom[2];
-        ev[13] += rr[1] * mom[2] - rr[2] * mom[1];
-        ev[14] += rr[2] * mom[0] - rr[0] * mom[2];
-        ev[15] += rr[0] * mom[1] - rr[1] * mom[0];
-        ev[16] += rb[0];
-        ev[17] += rb[1];
-        ev[18] += 1.0;
-    }
-    block_sum<B, 20>(ev, red);
     if (t == 0) {
-        double *pp = a.part3 + D.part3_off + (int64_t)local * PART;
-        for (int k = 0; k < 20; k++) pp[k] = ev[k];
+        put_dev(pp + 9, (double)nsolid);
+        put_dev(pp + 20, events ? 1.0 : 0.0);
     }
-    if constexpr (APART) return;
+    // the partials have left for device-visible memory before the count below
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
     // the counter of the group's primary entry counts the workgroups of every
     // sphere in the fluid (a single sphere: its own)
     RepState *sp = a.state + D.primary;
-    __threadfence();
+    if (t == 0)
+        sh.last = __hip_atomic_fetch_add(&sp->k3_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                  (unsigned)(D.k3_total - 1);
     __syncthreads();
-    if (t == 0) last = (atomicAdd(&sp->k3_done, 1u) == (unsigned)(D.k3_total - 1));
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
+    if (!sh.last) return;
     // the next launch sees the stores below: kernel boundaries order them
     if (D.n_sph > 1) {
-        publish_group(a, D.primary, g);
-        if (t == 0) sp->k3_done = 0;
+        publish_group(a, D.primary, g, sh, ev, t);
         return;
     }
     // last workgroup: event sums (fixed order), then the new state
-    double tot[20];
-    sum_partials<20>(a.part3 + D.part3_off, D.k3_count, 0, tot);
-    if (t != 0) return;
-    st->k3_done = 0;
-    publish_step(a, D, st, g, sum, mo, tot);
-}
-
-// ============================================================== k_finish
-// One wave per entry after k_particle (finish_apart): sums the link and
-// event partials in the same fixed order, repeats the Newton-Euler step of
-// k_particle on the same inputs and publishes the state of step n+1 (a
-// group of spheres in one fluid: its primary's wave publishes them all).
-template <int B>
-__global__ __launch_bounds__(B) void k_finish(ParticleArgs a) {
-    const int r = blockIdx.x;
-    const RepDesc *__restrict__ dp = a.desc + r;  // read-only in this kernel
-    const RepDesc &D = *dp;
-    RepState *st = a.state + r;
-    if (!D.has_particle) {
-        if (threadIdx.x == 0) advance_empty(a, D, st);
-        return;
-    }
-    const Geo g = geo_of(D);
-    if (D.n_sph > 1) {
-        if (D.primary == r) publish_group(a, r, g);
-        return;
-    }
-    double sum[15], tot[20];
-    sum_partials<15>(a.part1 + D.part3_off, D.k3_count, 0, sum);
-    sum_partials<20>(a.part3 + D.part3_off, D.k3_count, 0, tot);
-    Motion mo;
-    newton_euler(D, st, g, sum, mo);
-    if (threadIdx.x == 0) publish_step(a, D, st, g, sum, mo, tot);
+    event_totals(a.part3 + D.part3_off, D.k3_count, sh, ev, t);
+    publish_step(a, D, st, g, sh, t);
 }
 
 // ================================================================ k_init
@@ -1603,17 +1802,13 @@ hipError_t launch_main_t(const MainArgs &a, int grid, int block, size_t lds, hip
 
 template <typename S, typename T>
 hipError_t launch_links_t(const LinkArgs &a, int grid, hipStream_t s) {
-    hipLaunchKernelGGL((k_links<S, T, K3_THREADS>), dim3(grid), dim3(K3_THREADS), 0, s, a);
+    hipLaunchKernelGGL((k_links<S, T>), dim3(grid), dim3(K3_THREADS), 0, s, a);
     return hipGetLastError();
 }
 
 template <typename S, typename T>
 hipError_t launch_particle_t(const ParticleArgs &a, int grid, hipStream_t s) {
-    if (a.finish_apart) hipLaunchKernelGGL((k_particle<S, T, K3_THREADS, true>), dim3(grid), dim3(K3_THREADS), 0, s, a);
-    else hipLaunchKernelGGL((k_particle<S, T, K3_THREADS, false>), dim3(grid), dim3(K3_THREADS), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !a.finish_apart) return e;
-    hipLaunchKernelGGL(k_finish<64>, dim3(a.nrep), dim3(64), 0, s, a);
+    hipLaunchKernelGGL((k_particle<S, T>), dim3(grid), dim3(K3_THREADS), 0, s, a);
     return hipGetLastError();
 }
 
