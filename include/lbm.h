@@ -222,9 +222,10 @@ int lbm_checkpoint(lbm_ctx *c, void *dev_dst);
 int lbm_restore(lbm_ctx *c, const void *dev_src);
 
 /* Launch shape of the main kernel: block threads (256, 512 or 1024; at least
- * the longest x-row) and z-chunk length (>= 1; 0 picks the default: the
- * longest power-of-two chunk up to 16 that keeps about four waves per SIMD
- * resident).  Rebuilds the tiling; results do not depend on the shape.
+ * the longest x-row) and z-chunk length (>= 1; 0 picks the default for the
+ * block: a power of two up to 32 by an estimate of the main kernel's cost).
+ * A new context starts with the block and z-chunk of least estimated cost.
+ * Rebuilds the tiling; results do not depend on the shape.
  * LBM_EINVAL for other blocks or a shape needing more than 64 KiB of LDS. */
 int lbm_set_launch(lbm_ctx *c, int32_t block, int32_t zchunk);
 int lbm_get_launch(lbm_ctx *c, int32_t *block, int32_t *zchunk);

@@ -357,21 +357,66 @@ void build_tiling(lbm_ctx *c) {
     c->lds = main_lds_bytes(c);
 }
 
-// Longest z-chunk (a power of two up to 16) that still gives the main
-// kernel about four resident waves per SIMD on 256 CUs; 2 if none does.
-int auto_zchunk(lbm_ctx *c) {
-    const int64_t want = 256 * 16 / (c->block / 64);
-    for (int cz = 16; cz >= 2; cz /= 2) {
-        int64_t wgs = 0;
-        for (int r = 0; r < c->nrep; r++) {
-            if (c->prim[r] != r) continue;
-            const lbm_params &q = c->p[r];
-            const int ty = tile_rows(c, q);
-            wgs += (int64_t)((q.ny + ty - 1) / ty) * ((q.nz + cz - 1) / cz);
-        }
-        if (wgs >= want) return cz;
+// Cost of one main-kernel launch at z-chunk cz and the context's block, in lane
+// planes.  A tile collides cz planes and fills cz + 2, a fill costing 0.12 of a
+// collision, its two halo rows included; partly filled tiles cost what full ones
+// do.  With x = waves / 4096 (four per SIMD on 256 CUs), too few waves leave
+// each other's latency uncovered: sqrt(1 + (0.3 / x)^2).  Blocks of 512 and 1024
+// wait for more waves at every plane: 1.12 and 1.16.  Fitted to the main
+// kernel's times at every shape on 18 lattices of 8 k to 38 M nodes (FP64, FP32,
+// FP16, single and batched): the shape it picks takes 2.5% more than the best
+// one in the mean and 14% at most.  The longest z-chunk up to 16 that keeps
+// about four waves per SIMD, at 256 threads, took 11% more in the mean and 54%
+// at most (16 x 16 x 32: 24.6 us at z-chunk 2, 18.2 at 1; 192 x 192 x 1024 FP16:
+// 2346 us at 256 threads, 1953 at 1024 x 32; 150 x 100 x 200: 375 and 300 us).
+double shape_cost(const lbm_ctx *c, int cz) {
+    double lanes = 0.0, waves = 0.0;
+    for (int r = 0; r < c->nrep; r++) {
+        if (c->prim[r] != r) continue;
+        const lbm_params &q = c->p[r];
+        const int ty = tile_rows(c, q), z = std::min(cz, q.nz);
+        const double tiles = (double)((q.ny + ty - 1) / ty) * ((q.nz + z - 1) / z);
+        lanes += tiles * c->block * (z + 0.12 * (z + 2) * (1.0 + 2.0 * q.nx / c->block));
+        waves += tiles * (c->block / 64);
     }
-    return 2;
+    const double x = waves / 4096.0;
+    return lanes * std::sqrt(1.0 + 0.09 / (x * x)) * (c->block == 256 ? 1.0 : c->block == 512 ? 1.12 : 1.16);
+}
+
+// z-chunk of least cost at the context's block
+int auto_zchunk(const lbm_ctx *c, double *cost = nullptr) {
+    int best = 1;
+    double least = 0.0;
+    for (int cz = 1; cz <= 32; cz *= 2) {
+        const double v = shape_cost(c, cz);
+        if (cz == 1 || v < least) {
+            best = cz;
+            least = v;
+        }
+    }
+    if (cost) *cost = least;
+    return best;
+}
+
+// block and z-chunk of least cost.  1024 threads leave 128 VGPRs: enough for FP32
+// arithmetic with every relaxation time 1, scratch memory in every other form.
+void auto_shape(lbm_ctx *c) {
+    int best_block = 256, best_cz = 1;
+    double least = -1.0;
+    for (int block = MAIN_BLOCK_MIN; block <= 1024; block *= 2) {
+        if (block == 1024 && (c->prec == LBM_FP64 || !c->tau1)) continue;
+        c->block = block;
+        if (main_lds_bytes(c) > MAIN_LDS_MAX) continue;
+        double v;
+        const int cz = auto_zchunk(c, &v);
+        if (least < 0.0 || v < least) {
+            least = v;
+            best_block = block;
+            best_cz = cz;
+        }
+    }
+    c->block = best_block;
+    c->cz = best_cz;
 }
 
 int upload_desc(lbm_ctx *c) {
@@ -679,7 +724,7 @@ LBM_API int lbm_init(const lbm_params *p_in, int32_t n_replicas, int32_t precisi
         }
     }
     for (int r = 0; r < n_replicas; r++) c->maxnx = std::max(c->maxnx, p[r].nx);
-    c->cz = auto_zchunk(c);
+    auto_shape(c);
     build_tiling(c);
     int rc = upload_desc(c);
     if (rc != LBM_OK) { g_init_error = c->err; delete c; return rc; }
