@@ -11,8 +11,8 @@
 //
 // Storage.  Each replica keeps its populations on a lattice with one ghost row
 // per y side and one ghost plane per z side, laid out
-// [z+1][y+1][component][direction][x]: the 38 slots of an x-row lie next to
-// each other, rows follow without padding.  Node x pulls population i of step
+// [z+1][y+1][slot][x]: the 38 slots (component and direction) of an x-row lie
+// next to each other, rows follow without padding.  Node x pulls population i of step
 // n from position x - c_i, slot i, x wrapped around the row; a node whose
 // x - c_i lies beyond an x-wall pulls slot opp(i) of itself (half-way
 // bounce-back).  Whoever produces a value that does not arrive that way writes
@@ -85,7 +85,50 @@ __device__ __forceinline__ Geo geo_of(const RepDesc &D) {
 __device__ __forceinline__ int row_stride(const Geo &g) { return 2 * Q * g.nx; }
 __device__ __forceinline__ int plane_stride(const Geo &g) { return 2 * Q * g.nx * (g.ny + 2); }
 
-// element of slot s (19 l + i) at position (x, y, z), 0 <= x < nx, -1 <= y <= ny, -1 <= z <= nz
+// Slot of population i of component l within a row.  Slots that are pulled from
+// the same row and plane, i.e. of equal (c_y, c_z), are neighbours: where a
+// slot's nx elements are no whole cache lines, two slots share a line, and one
+// that is pulled a row or a plane later than the other is fetched twice.
+// Read requests of L2 to memory, in order of (component, direction) and so:
+// ensemble (32, 24 and 48 node rows) 7.5e7 and 6.6e7 per step, 60 x 60 x 900 7.6e6
+// and 6.4e6.
+struct SlotOf {
+    int s, n;  // slot of component A; component B's is n further
+};
+constexpr SlotOf slot_of(int i) {
+    constexpr int order[9][2] = {{0, 0}, {1, 0}, {-1, 0}, {0, 1}, {1, 1}, {-1, 1}, {0, -1}, {1, -1}, {-1, -1}};
+    int at = 0;
+    for (int k = 0; k < 9; k++) {
+        int n = 0, idx = -1;
+        for (int j = 0; j < Q; j++) {
+            if (cy(j) != order[k][0] || cz(j) != order[k][1]) continue;
+            if (j == i) idx = n;
+            n++;
+        }
+        if (idx >= 0) return {at + idx, n};
+        at += 2 * n;
+    }
+    return {0, 0};
+}
+struct SlotTable {
+    int s[Q], n[Q];
+    int dir[Q];  // directions in the order of their slots
+};
+constexpr SlotTable make_slots() {
+    SlotTable t{};
+    for (int i = 0; i < Q; i++) {
+        t.s[i] = slot_of(i).s;
+        t.n[i] = slot_of(i).n;
+        int before = 0;
+        for (int j = 0; j < Q; j++) before += slot_of(j).s < slot_of(i).s;
+        t.dir[before] = i;
+    }
+    return t;
+}
+constexpr SlotTable SLOTS = make_slots();
+__device__ __forceinline__ constexpr int slot(int l, int i) { return SLOTS.s[i] + l * SLOTS.n[i]; }
+
+// element of slot s at position (x, y, z), 0 <= x < nx, -1 <= y <= ny, -1 <= z <= nz
 __device__ __forceinline__ int64_t slot_at(int x, int y, int z, int s, const Geo &g) {
     return (int64_t)(z + 1) * plane_stride(g) + (int64_t)(y + 1) * row_stride(g) + s * g.nx + x;
 }
@@ -93,9 +136,9 @@ __device__ __forceinline__ int64_t slot_at(int x, int y, int z, int s, const Geo
 // element that node (x, y, z) pulls population i of component l from
 __device__ __forceinline__ int64_t pull_slot(int x, int y, int z, int l, int i, const Geo &g) {
     const int sx = x - cx(i);
-    if (sx >= 0 && sx < g.nx) return slot_at(sx, y - cy(i), z - cz(i), l * Q + i, g);
-    if (g.wx) return slot_at(x, y, z, l * Q + opp(i), g);
-    return slot_at(sx < 0 ? sx + g.nx : sx - g.nx, y - cy(i), z - cz(i), l * Q + i, g);
+    if (sx >= 0 && sx < g.nx) return slot_at(sx, y - cy(i), z - cz(i), slot(l, i), g);
+    if (g.wx) return slot_at(x, y, z, slot(l, opp(i)), g);
+    return slot_at(sx < 0 ? sx + g.nx : sx - g.nx, y - cy(i), z - cz(i), slot(l, i), g);
 }
 // unpadded node index (noise counter, fields)
 __device__ __forceinline__ uint32_t nidx(int x, int y, int z, const Geo &g) {
@@ -230,9 +273,10 @@ __device__ __forceinline__ void buf_st(S v, Rsrc r, uint32_t vo, uint32_t so) {
 // scalar registers do not hold every derived offset at once)
 __device__ __forceinline__ void renew(int32_t &v) { asm volatile("" : "+s"(v)); }
 
-// Components L0 .. L0 + NL - 1 of a node; z uniform over the wave, (x, y) per lane.
-template <int NL, typename S, typename T>
-__device__ __forceinline__ void pull_row(PullCtx<S, T> c, int x, int y, int z, int L0, T (&d)[NL][Q]) {
+// Components L0 .. L0 + NL - 1 of a node; z uniform over the wave, (x, y) per
+// lane.  As numbers T, or unscaled as they are stored (FP16, S = E).
+template <int NL, typename E, typename S, typename T>
+__device__ __forceinline__ void pull_row(PullCtx<S, T> c, int x, int y, int z, int L0, E (&d)[NL][Q]) {
     constexpr uint32_t es = sizeof(S);
     renew(c.nx);
     renew(c.RS);
@@ -247,20 +291,22 @@ __device__ __forceinline__ void pull_row(PullCtx<S, T> c, int x, int y, int z, i
     const uint32_t vm = lo ? own + (nxb - es) : own - es, vp = hi ? own - (nxb - es) : own + es;
     const bool wm = c.wx && lo, wp = c.wx && hi;
 #pragma unroll
-    for (int i = 0; i < Q; i++) {
+    for (int k = 0; k < Q; k++) {
+        const int i = SLOTS.dir[k];
         const T w = T(wgt(i));
         uint32_t vo = (cx(i) > 0 ? vm : cx(i) < 0 ? vp : own) + (cz(i) < 0 ? PSb : 0u);
         if (cx(i)) {
             // across an x-wall: the node's own slot opp(i), in plane z
-            const uint32_t k = (opp(i) > i ? nxb : 0u - nxb) + (cy(i) > 0 ? RSb : cy(i) < 0 ? 0u - RSb : 0u) +
+            const uint32_t up = (uint32_t)(slot(0, opp(i)) - slot(0, i)) * nxb + (cy(i) > 0 ? RSb : cy(i) < 0 ? 0u - RSb : 0u) +
                                (cz(i) > 0 ? PSb : 0u);
-            vo = (cx(i) > 0 ? wm : wp) ? own + k : vo;
+            vo = (cx(i) > 0 ? wm : wp) ? own + up : vo;
         }
-        const uint32_t so = (uint32_t)(1 - cy(i)) * RSb + (uint32_t)(L0 * Q + i) * nxb;
+        const uint32_t so = (uint32_t)(1 - cy(i)) * RSb + (uint32_t)slot(L0, i) * nxb;
 #pragma unroll
         for (int l = 0; l < NL; l++) {
-            const S v = buf_ld<S>(cz(i) > 0 ? r1 : r0, vo, so + (uint32_t)(l * Q) * nxb);
-            d[l][i] = ld_dev<S, T>(&v, w * (L0 + l ? c.scale[1] : c.scale[0]));
+            const S v = buf_ld<S>(cz(i) > 0 ? r1 : r0, vo, so + (uint32_t)(l * SLOTS.n[i]) * nxb);
+            if constexpr (Rel<S>::value && sizeof(E) == sizeof(S)) d[l][i] = v;
+            else d[l][i] = ld_dev<S, T>(&v, w * (L0 + l ? c.scale[1] : c.scale[0]));
         }
     }
 }
@@ -274,10 +320,10 @@ __device__ __forceinline__ void pull_node(const PullCtx<S, T> &c, int x, int y, 
 #pragma unroll
     for (int i = 0; i < Q; i++) {
         const T w = T(wgt(i));
-        int32_t off = i * c.nx - cy(i) * c.RS - cz(i) * c.PS + (cx(i) > 0 ? dm : cx(i) < 0 ? dp : 0);
-        if (cx(i)) off = c.wx && (cx(i) > 0 ? lo : hi) ? opp(i) * c.nx : off;
+        int32_t off = slot(0, i) * c.nx - cy(i) * c.RS - cz(i) * c.PS + (cx(i) > 0 ? dm : cx(i) < 0 ? dp : 0);
+        if (cx(i)) off = c.wx && (cx(i) > 0 ? lo : hi) ? slot(0, opp(i)) * c.nx : off;
         d[0][i] = ld_dev<S, T>(own + off, w * c.scale[0]);
-        d[1][i] = ld_dev<S, T>(own + off + Q * c.nx, w * c.scale[1]);
+        d[1][i] = ld_dev<S, T>(own + off + SLOTS.n[i] * c.nx, w * c.scale[1]);
     }
 }
 
@@ -301,6 +347,28 @@ __device__ __forceinline__ void node_moments(const T (&d)[2][Q], NodeM<T> &s) {
             if (cz(i) > 0) jz += d[l][i]; else if (cz(i) < 0) jz -= d[l][i];
         }
         s.rd[l] = r; s.j[l][0] = jx; s.j[l][1] = jy; s.j[l][2] = jz;
+    }
+}
+
+// The same from relative deviations h = d / (w_i rho0_l): each sum takes the
+// weight in its multiply-add, which reads the 16-bit value as it is stored (49
+// operations per component against 87 with a conversion and a product first).
+template <typename T>
+__device__ __forceinline__ void node_moments_rel(const T (&h)[2][Q], const T (&rho0)[2], NodeM<T> &s) {
+#pragma unroll
+    for (int l = 0; l < 2; l++) {
+        T r = T(0), j[3] = {T(0), T(0), T(0)};
+#pragma unroll
+        for (int i = 0; i < Q; i++) {
+            const T w = T(wgt(i));
+            r = fma(h[l][i], w, r);
+            if (cx(i)) j[0] = fma(h[l][i], cx(i) > 0 ? w : -w, j[0]);
+            if (cy(i)) j[1] = fma(h[l][i], cy(i) > 0 ? w : -w, j[1]);
+            if (cz(i)) j[2] = fma(h[l][i], cz(i) > 0 ? w : -w, j[2]);
+        }
+        s.rd[l] = r * rho0[l];
+#pragma unroll
+        for (int q = 0; q < 3; q++) s.j[l][q] = j[q] * rho0[l];
     }
 }
 
@@ -416,9 +484,10 @@ void k_main(MainArgs a) {
     const int z0 = ch * zc, z1 = min(z0 + zc, g.nz);
     const int t = threadIdx.x;
     const int nin = nx * rows;
-    const bool inner = t < nin;
-    const int x = inner ? t % nx : 0, yl = inner ? t / nx : 0;
-    const int y = y0 + yl;
+    // this lane's node: x and, in the upper half, its row of the tile (0x4000 and
+    // more: none).  Kept packed, and what follows from it formed per plane, since
+    // hoisted coordinates, neighbours and face masks cost 20 VGPRs.
+    uint32_t pos = t < nin ? (uint32_t)(t % nx) | (uint32_t)(t / nx) << 16 : 0x40000000u;
     const int pr = (ty + 2) * nx;  // LDS elements per plane and component
 
     const bool hp = D.has_particle;
@@ -449,12 +518,19 @@ void k_main(MainArgs a) {
         return lds[(slot * 2 + l) * pr + (row + 1) * nx + xx];
     };
 
+    // whether plane z meets the sphere's box (uniform; with several spheres: may)
+    auto box_plane = [&](int z) -> bool {
+        int bz = z - org[2];
+        if (!g.wz) bz = bz < 0 ? bz + g.nz : (bz >= g.nz ? bz - g.nz : bz);
+        return hp && ((GROUP && nsph > 1) || (uint32_t)bz < (uint32_t)Sx);
+    };
+
     // density deviation of a box node: pulled (plus the mass correction), or
     // the wetting-layer value on particle nodes; fluid nodes also return
-    // their moments
-    auto node_density = [&](int xx, int yy, int zz, NodeM<T> &s, T &rA, T &rB) -> bool {
+    // their moments (have: the node's populations, if they are loaded already)
+    auto node_density = [&](int xx, int yy, int zz, bool zbox, const S(*have)[Q], NodeM<T> &s, T &rA, T &rB) -> bool {
         int b = -1;
-        if (hp) b = bbox_index(xx, yy, zz, org, Sx, g);
+        if (zbox) b = bbox_index(xx, yy, zz, org, Sx, g);
         if (b < 0 || !(pmask[b] & MASK_SOLID)) {
             // the group's other spheres (their boxes are disjoint from this
             // one's and from each other, so at most one holds the node)
@@ -475,8 +551,22 @@ void k_main(MainArgs a) {
             }
             if (vi < 0) {
                 T d[2][Q];
-                pull_row<2>(pcl, xx, yy, zz, 0, d);
-                node_moments(d, s);
+                if constexpr (TAU1) {
+                    S raw[2][Q];
+                    if (!have) pull_row<2>(pcl, xx, yy, zz, 0, raw);
+#pragma unroll
+                    for (int i = 0; i < Q; i++) {
+                        d[0][i] = T(have ? have[0][i] : raw[0][i]);
+                        d[1][i] = T(have ? have[1][i] : raw[1][i]);
+                    }
+                    if constexpr (Rel<S>::value) node_moments_rel(d, pcl.scale, s);
+                    else node_moments(d, s);
+                } else {
+                    pull_row<2>(pcl, xx, yy, zz, 0, d);
+                    T unused[Q];
+                    component_modes(d[0], s.rd[0], s.j[0], unused);
+                    component_modes(d[1], s.rd[1], s.j[1], unused);
+                }
                 s.rd[0] += dl[0];
                 s.rd[1] += dl[1];
                 rA = s.rd[0];
@@ -495,12 +585,30 @@ void k_main(MainArgs a) {
     NodeM<T> nxt;
     bool nxt_fluid = false;
 
+    // FP32, all relaxation times 1: the next plane's populations of this lane's
+    // node are loaded while the current plane collides (38 registers, which the
+    // packed position leaves room for at four waves per SIMD), so that memory is
+    // busy in the collision phase too.  Measured without and with: 60 x 60 x 900
+    // 296 -> 290 us, 192 ensemble channels 2464 -> 2400, 8 x (32 x 32 x 128) 61.1 ->
+    // 58.8, 64 x 64 x 256 86.7 -> 85.4.  FP16 storage loses by it (192 x 192 x 1024:
+    // 1912 -> 2082 us; bound by the vector ALU, and each 16-bit number held takes a
+    // register), and the general and FP64 forms have no registers left.
+    constexpr bool PREF = main_fast_form<S, T, TAU1> && sizeof(S) == 4;
+    S pre[2][Q];
+    auto prefetch = [&](int zp) {
+        const int zz = mirror1(zp, g.nz, g.wz);
+        const int x = (int)(pos & 0xffffu), yl = (int)(pos >> 16);
+        if (yl < 0x4000) pull_row<2>(pcl, x, y0 + yl, zz, 0, pre);
+        __builtin_amdgcn_sched_barrier(0);
+    };
     // fill LDS plane zp (unmapped index); the interior node's moments go to nxt
     auto fill = [&](int zp) {
         const int zz = mirror1(zp, g.nz, g.wz);
-        if (inner) {
+        const bool zbox = box_plane(zz);
+        const int x = (int)(pos & 0xffffu), yl = (int)(pos >> 16);
+        if (yl < 0x4000) {
             T rA, rB;
-            nxt_fluid = node_density(x, y, zz, nxt, rA, rB);
+            nxt_fluid = node_density(x, y0 + yl, zz, zbox, PREF ? pre : nullptr, nxt, rA, rB);
             L(zp, 0, yl, x) = rA;
             L(zp, 1, yl, x) = rB;
         }
@@ -511,16 +619,11 @@ void k_main(MainArgs a) {
             const int yy = mirror1(y0 + row, g.ny, g.wy);
             NodeM<T> hd;
             T rA, rB;
-            node_density(xx, yy, zz, hd, rA, rB);
+            node_density(xx, yy, zz, zbox, nullptr, hd, rA, rB);
             L(zp, 0, row, xx) = rA;
             L(zp, 1, row, xx) = rB;
         }
     };
-
-    const int xm = mirror1(x - 1, nx, g.wx), xp = mirror1(x + 1, nx, g.wx);
-    // x / y faces of this lane's node as bits (x low, x high, y low, y high)
-    uint32_t xyface = (x == 0 ? 1u : 0u) | (x == nx - 1 ? 2u : 0u) | (y == 0 ? 4u : 0u) |
-                      (y == g.ny - 1 ? 8u : 0u);
 
     // Plane zp is filled while the plane filled before it collides.  Odd
     // z-chunks march downwards, so two neighbouring chunks read the halo
@@ -529,21 +632,25 @@ void k_main(MainArgs a) {
     const int dir = (ch & 1) ? -1 : 1;
     const int zfirst = dir > 0 ? z0 - 1 : z1;
     const int nplanes = z1 - z0 + 2;
+    if constexpr (PREF) prefetch(zfirst);
     for (int k = 0; k < nplanes; k++) {
         // keep uniform values derived from these roots inside the loop (scalar
         // recomputation is cheaper than spilling hoisted copies)
         asm volatile("" : "+s"(k0), "+s"(k1), "+s"(pcl.nx), "+s"(pcl.RS), "+s"(pcl.PS));
-        // face tests are redone per plane from these bits instead of being
-        // hoisted as lane masks that would crowd the scalar registers
-        asm volatile("" : "+v"(xyface));
+        asm volatile("" : "+v"(pos));
         const int zp = zfirst + dir * k;
         const NodeM<T> cur = nxt;
         const bool cur_fluid = nxt_fluid;
         fill(zp);
         __syncthreads();
+        if constexpr (PREF)
+            if (k + 1 < nplanes) prefetch(zp + dir);
         if (k < 2) continue;
         const int z = zp - dir;
-        if (inner && cur_fluid) {
+        const int x = (int)(pos & 0xffffu), yl = (int)(pos >> 16), y = y0 + yl;
+        if (yl < 0x4000 && cur_fluid) {
+            const int xm = mirror1(x - 1, nx, g.wx), xp = mirror1(x + 1, nx, g.wx);
+            const bool ylo = y == 0, yhi = y == g.ny - 1;
             const T(&rd)[2] = cur.rd;
             const T(&j)[2][3] = cur.j;
             // Shan-Chen: F_l = -G rho_l sum_i w_i rho~_l'(x + c_i) c_i + rho_l a_f
@@ -562,7 +669,7 @@ void k_main(MainArgs a) {
             }
             const T rl[2] = {cf.rho0[0] + rd[0], cf.rho0[1] + rd[1]};
             if (!(rl[0] > T(0)) || !(rl[1] >= T(0))) atomicOr(&stp->flags, FLAG_UNSTABLE);
-            if (hp) {  // densities near the spheres, for the link kernel
+            if (box_plane(z)) {  // densities near the spheres, for the link kernel
                 const int b = bbox_index(x, y, z, org, Sx, g);
                 if (b >= 0) {
                     rho_n[b] = (double)rl[0];
@@ -593,7 +700,7 @@ void k_main(MainArgs a) {
             else zz[32] = zz[33] = zz[34] = T(0);
             common_velocity(rd, j, F, zz, cf, u, xid);
             const bool zlo = z == 0, zhi = z == g.nz - 1;
-            const bool yzface = (xyface & 12u) != 0u || zlo || zhi;
+            const bool yzface = ylo || yhi || zlo || zhi;
             S *dplane = dst + (int64_t)(z + 1) * pcl.PS;
             const Rsrc drs = rsrc_of(dplane);
             const uint32_t own = ((uint32_t)(y + 1) * (uint32_t)pcl.RS + (uint32_t)x) * (uint32_t)sizeof(S);
@@ -625,10 +732,15 @@ void k_main(MainArgs a) {
                 }
                 T out[Q];
                 if constexpr (TAU1) {
-                    relax_tau1(r0l, sig, rdl, jl, Fl, u, xid, zl, cf, out);
+                    if constexpr (Rel<S>::value) relax_tau1_rel(r0l, sig, rdl, jl, Fl, u, xid, zl, cf, out);
+                    else relax_tau1(r0l, sig, rdl, jl, Fl, u, xid, zl, cf, out);
                 } else {
                     T ml[Q], rdm, jm[3];
                     component_modes(dl1[0], rdm, jm, ml);
+                    // each mode a number of its own: fused into the relaxation the
+                    // sums would round differently from form to form
+#pragma unroll
+                    for (int k = 4; k < Q; k++) asm("" : "+v"(ml[k]));
                     relax_component(r0l, sig, rdl, jl, ml, Fl, u, xid, zl, cf, out);
                 }
                 const T sc = Rel<S>::value ? r0l : T(1);
@@ -637,10 +749,10 @@ void k_main(MainArgs a) {
                 const uint32_t nxb = (uint32_t)nxs * (uint32_t)sizeof(S);
 #pragma unroll
                 for (int i = 0; i < Q; i++) {
-                    const T inv = Rel<S>::value ? T(1) / (T(wgt(i)) * sc) : T(1);
+                    const T inv = Rel<S>::value && !TAU1 ? T(1) / (T(wgt(i)) * sc) : T(1);
                     S v;
                     st_dev<S, T>(&v, out[i], inv);
-                    buf_st<S>(v, drs, own, (uint32_t)(l * Q + i) * nxb);
+                    buf_st<S>(v, drs, own, (uint32_t)slot(l, i) * nxb);
                 }
                 // A link that leaves the box through a y- or z-face also writes its
                 // value where the receiver pulls it from: the wall ghost x + c_i,
@@ -648,11 +760,11 @@ void k_main(MainArgs a) {
                 // slot i.  (Through an x-face alone it is pulled from the node's
                 // own slot, and across an x-wall whatever the other axes are.)
                 if (yzface) {
-                    const bool xlo = xyface & 1u, xhi = xyface & 2u, ylo = xyface & 4u, yhi = xyface & 8u;
+                    const bool xlo = x == 0, xhi = x == nx - 1;
 #pragma unroll
                     for (int i = 1; i < Q; i++) {
                         if (cy(i) == 0 && cz(i) == 0) continue;
-                        const T inv = Rel<S>::value ? T(1) / (T(wgt(i)) * sc) : T(1);
+                        const T inv = Rel<S>::value && !TAU1 ? T(1) / (T(wgt(i)) * sc) : T(1);
                         const bool ex = cx(i) > 0 ? xhi : (cx(i) < 0 ? xlo : false);
                         const bool ey = cy(i) > 0 ? yhi : (cy(i) < 0 ? ylo : false);
                         const bool ez = cz(i) > 0 ? zhi : (cz(i) < 0 ? zlo : false);
@@ -660,10 +772,10 @@ void k_main(MainArgs a) {
                             const bool bounce = (ey && g.wy) || (ez && g.wz);
                             const int32_t dx = ex ? cx(i) * (1 - nx) : cx(i);
                             const int64_t so =
-                                bounce ? (int64_t)(opp(i) * pcl.nx + cy(i) * pcl.RS + dx) + (int64_t)cz(i) * pcl.PS
-                                       : (int64_t)(i * pcl.nx) - (int64_t)(ey ? cy(i) * g.ny : 0) * pcl.RS -
+                                bounce ? (int64_t)(slot(l, opp(i)) * pcl.nx + cy(i) * pcl.RS + dx) + (int64_t)cz(i) * pcl.PS
+                                       : (int64_t)(slot(l, i) * pcl.nx) - (int64_t)(ey ? cy(i) * g.ny : 0) * pcl.RS -
                                              (int64_t)(ez ? cz(i) * g.nz : 0) * pcl.PS;
-                            S *base = dplane + l * Q * pcl.nx;
+                            S *base = dplane;
                             st_dev<S, T>(reinterpret_cast<S *>(reinterpret_cast<char *>(base + so) + own), out[i], inv);
                         }
                     }
@@ -786,9 +898,19 @@ constexpr uint32_t dir_bits(int ax, int m) {  // c + 1 of the four directions 5 
     }
     return v;
 }
+constexpr uint32_t slot_bits(bool against, int m) {  // their slots (or their opposites'), one byte each; bit 7: n = 3
+    uint32_t v = 0;
+    for (int q = 0; q < 4; q++) {
+        const int i = QM * q + m < Q ? QM * q + m : 0;
+        const SlotOf s = slot_of(against ? opp(i) : i);
+        v |= (uint32_t)(s.s | (s.n == 3 ? 0x80 : 0)) << (8 * q);
+    }
+    return v;
+}
 struct QDir {
     int c[3];
-    int i, io;      // direction and its opposite
+    int i;          // direction
+    int s, so, n;   // its slot and its opposite's (component A), step to component B
     bool valid;     // a moving direction (i = 1 .. 18)
 };
 template <int M>
@@ -799,14 +921,16 @@ __device__ __forceinline__ QDir quad_dir(int q) {
     d.c[1] = (int)((by >> (2 * q)) & 3u) - 1;
     d.c[2] = (int)((bz >> (2 * q)) & 3u) - 1;
     d.i = QM * q + M;
-    d.io = (d.i & 1) ? d.i + 1 : d.i - 1;
-    if (M == 0 && q == 0) d.io = 0;
+    constexpr uint32_t bs = slot_bits(false, M), bo = slot_bits(true, M);
+    d.s = (int)((bs >> (8 * q)) & 63u);
+    d.so = (int)((bo >> (8 * q)) & 63u);
+    d.n = (bs >> (8 * q)) & 0x80u ? 3 : 1;
     d.valid = M == 0 ? q != 0 : M == QM - 1 ? q != 3 : true;
     return d;
 }
-// the direction against d
+// the direction against d (its number is not needed)
 __device__ __forceinline__ QDir against(const QDir &d) {
-    return {{-d.c[0], -d.c[1], -d.c[2]}, d.io, d.i, d.valid};
+    return {{-d.c[0], -d.c[1], -d.c[2]}, -1, d.so, d.s, d.n, d.valid};
 }
 // w_i of direction 5 q + M
 template <int M>
@@ -919,8 +1043,8 @@ __device__ __forceinline__ int pull_off(int x, const QDir &d, const Geo &g) {
     const int sx = x - d.c[0];
     const bool out = sx < 0 || sx >= g.nx;
     const int wr = sx < 0 ? g.nx : (out ? -g.nx : 0);
-    const int off = d.i * g.nx - d.c[1] * row_stride(g) - d.c[2] * plane_stride(g) - d.c[0] + wr;
-    return (out && g.wx) ? d.io * g.nx : off;
+    const int off = d.s * g.nx - d.c[1] * row_stride(g) - d.c[2] * plane_stride(g) - d.c[0] + wr;
+    return (out && g.wx) ? d.so * g.nx : off;
 }
 
 // Sum of 64 numbers v[0 .. 63] by the 16 threads s = 0 .. 15 of a DPP row, as
@@ -995,15 +1119,15 @@ __global__ __launch_bounds__(K3_THREADS) void k_links(LinkArgs a) {
             constexpr int m = decltype(mc)::value;
             const QDir d = quad_dir<m>(q);
             const int off = d.i < Q ? pull_off(p[0], against(d), g) : 0;
-            const int ownoff = d.i < Q ? d.i * g.nx : 0;
+            const int ownoff = d.s * g.nx;
             int np[3];
             const int nbi = box_at(bb, d.c, Sx);
             ok[m] = d.valid && nbi >= 0 && step_to(p, d.c, g, np);
             const int nb = nbi >= 0 ? nbi : b;
 #pragma unroll
             for (int l = 0; l < 2; l++) {
-                dv[l][m] = row[off + l * Q * g.nx];
-                fv[l][m] = row[ownoff + l * Q * g.nx];
+                dv[l][m] = row[off + l * d.n * g.nx];
+                fv[l][m] = row[ownoff + l * d.n * g.nx];
                 rn[l][m] = rho_n[l * S3 + nb];
             }
             pm[m] = pmask[nb];
@@ -1038,7 +1162,7 @@ __global__ __launch_bounds__(K3_THREADS) void k_links(LinkArgs a) {
                     S sv;
                     v[l][m] = store_round<S, T>(fs - corr - wr, Rel<S>::value ? T(1.0 / wr) : T(1),
                                                 Rel<S>::value ? T(w) * T(rho0[l]) : T(1), sv);
-                    to[l * Q * g.nx] = sv;
+                    to[l * d.n * g.nx] = sv;
                 }
                 nlinks++;
             }
@@ -1551,7 +1675,7 @@ __global__ __launch_bounds__(K3_THREADS) void k_particle(ParticleArgs a) {
 #pragma unroll
                 for (int l = 0; l < 2; l++) {
                     const double wr = w * D.rho0[l];
-                    st_dev<S, T>(to + l * Q * g.nx, T(w * self[l] * e - wr), Rel<S>::value ? T(1.0 / wr) : T(1));
+                    st_dev<S, T>(to + l * d.n * g.nx, T(w * self[l] * e - wr), Rel<S>::value ? T(1.0 / wr) : T(1));
                 }
             });
         }
@@ -1703,8 +1827,8 @@ __global__ __launch_bounds__(256) void k_ck(CkArgs a) {
 #pragma unroll
         for (int l = 0; l < 2; l++) {
             S *c = ck + (int64_t)(l * Q + i) * D.ck_NP;
-            if constexpr (SAVE) *c = in ? p[l * Q * g.nx] : S(0);
-            else if (in) p[l * Q * g.nx] = *c;
+            if constexpr (SAVE) *c = in ? p[l * SLOTS.n[i] * g.nx] : S(0);
+            else if (in) p[l * SLOTS.n[i] * g.nx] = *c;
         }
     }
 }

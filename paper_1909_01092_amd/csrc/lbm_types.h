@@ -1,7 +1,7 @@
 // Device-side data layout of the library (workspace contents).
 //
 // Populations: two ping-pong buffers; replica r owns a block of
-// 38 nx (ny + 2)(nz + 2) elements laid out [z+1][y+1][component][direction][x]
+// 38 nx (ny + 2)(nz + 2) elements laid out [z+1][y+1][slot][x]
 // on its lattice with one ghost row per y side and one ghost plane per z side.
 // A buffer holds the post-collision values f*_i of the last step in the slot
 // each node pulls from (slot i at position x - c_i, x wrapped around its row;
