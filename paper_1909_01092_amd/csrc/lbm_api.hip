@@ -357,37 +357,49 @@ void build_tiling(lbm_ctx *c) {
     c->lds = main_lds_bytes(c);
 }
 
-// Cost of one main-kernel launch at z-chunk cz and the context's block, in lane
-// planes.  A tile collides cz planes and fills cz + 2, a fill costing 0.12 of a
-// collision, its two halo rows included; partly filled tiles cost what full ones
-// do.  With x = waves / 4096 (four per SIMD on 256 CUs), too few waves leave
-// each other's latency uncovered: sqrt(1 + (0.3 / x)^2).  Blocks of 512 and 1024
-// wait for more waves at every plane: 1.12 and 1.16.  Fitted to the main
-// kernel's times at every shape on 18 lattices of 8 k to 38 M nodes (FP64, FP32,
-// FP16, single and batched): the shape it picks takes 2.5% more than the best
-// one in the mean and 14% at most.  The longest z-chunk up to 16 that keeps
-// about four waves per SIMD, at 256 threads, took 11% more in the mean and 54%
-// at most (16 x 16 x 32: 24.6 us at z-chunk 2, 18.2 at 1; 192 x 192 x 1024 FP16:
-// 2346 us at 256 threads, 1953 at 1024 x 32; 150 x 100 x 200: 375 and 300 us).
+// Cost of one main-kernel launch at z-chunk cz and the context's block: the root
+// of the squares of two times, in planes that one wave collides.
+//  - Work of a compute unit: each of its workgroups collides cz planes and fills
+//    cz + 2, a fill costing half a collision, its two halo rows included; partly
+//    filled tiles cost what full ones do.  While all workgroups are resident
+//    (four waves per SIMD; two in FP64) the busiest unit holds a whole number of
+//    them; after that, 0.55 of what the last round leaves idle is lost.
+//  - Latency: a wave alone takes 2.4 times as long per plane as a SIMD's share.
+// Blocks of 512 and 1024 wait for more waves at every plane: 1.08 and 1.23.
+// Fitted to the main kernel's times at every shape on 29 lattices of 8 k to 38 M
+// nodes (all storages, both relaxations, single and batched): the shape it picks
+// takes 1.9% more than the best one in the mean and 11% at most.  A cost of total
+// work and waves alone, with z-chunks of powers of two, took 9.8% and 48% (91 x 21
+// x 266: 1024 x 2, 266 workgroups for 256 units, 82.7 us; 512 x 3 54.4), and the
+// longest z-chunk up to 16 that keeps four waves per SIMD at 256 threads 54% at
+// most (16 x 16 x 32: 24.6 us at z-chunk 2, 18.2 at 1; 192 x 192 x 1024 FP16: 2346
+// us at 256 threads, 1912 at 1024 x 32).
 double shape_cost(const lbm_ctx *c, int cz) {
-    double lanes = 0.0, waves = 0.0;
+    double work = 0.0, n = 0.0;
+    int longest = 0;
     for (int r = 0; r < c->nrep; r++) {
         if (c->prim[r] != r) continue;
         const lbm_params &q = c->p[r];
         const int ty = tile_rows(c, q), z = std::min(cz, q.nz);
         const double tiles = (double)((q.ny + ty - 1) / ty) * ((q.nz + z - 1) / z);
-        lanes += tiles * c->block * (z + 0.12 * (z + 2) * (1.0 + 2.0 * q.nx / c->block));
-        waves += tiles * (c->block / 64);
+        work += tiles * (z + 0.5 * (z + 2) * (1.0 + 2.0 * q.nx / c->block));
+        n += tiles;
+        longest = std::max(longest, z);
     }
-    const double x = waves / 4096.0;
-    return lanes * std::sqrt(1.0 + 0.09 / (x * x)) * (c->block == 256 ? 1.0 : c->block == 512 ? 1.12 : 1.16);
+    const int waves = c->block / 64;
+    const double resident = std::max(1, 4 * (c->prec == LBM_FP64 ? 2 : 4) / waves);
+    const double m = n / 256.0, rounds = std::ceil(m / resident);
+    const double share = std::ceil(m) <= resident ? std::ceil(m) : m + 0.55 * (rounds * resident - m);
+    const double busy = work / n * share * waves / 4.0 * (c->block == 256 ? 1.0 : c->block == 512 ? 1.08 : 1.23);
+    const double wait = 2.4 * (longest + 0.5 * (longest + 2)) * std::max(1.0, m / resident);
+    return std::sqrt(busy * busy + wait * wait);
 }
 
 // z-chunk of least cost at the context's block
 int auto_zchunk(const lbm_ctx *c, double *cost = nullptr) {
     int best = 1;
     double least = 0.0;
-    for (int cz = 1; cz <= 32; cz *= 2) {
+    for (const int cz : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32}) {
         const double v = shape_cost(c, cz);
         if (cz == 1 || v < least) {
             best = cz;
