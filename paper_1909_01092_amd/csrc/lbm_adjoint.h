@@ -29,6 +29,7 @@ struct AdjState {
     double Jsum;                 // sum of U_z^{n+1/2} over the reversed steps
     uint32_t done;               // completion counter of the wetting-chain kernel (0 between steps)
     uint32_t pad;
+    double sums[15];  // node-kernel and link sums of the step being reversed (k_adj_chain)
 };
 
 // Forward values of a fluid node at step n rebuilt from the recorded
@@ -42,8 +43,10 @@ struct NodeFwd {
 };
 constexpr size_t NODE_FWD_BYTES = sizeof(NodeFwd<double>);
 
-constexpr int ADJ_PA = 13;   // doubles per workgroup partial of the local kernel
+constexpr int ADJ_PA = 13;   // doubles of a link partial (stride PART per workgroup)
+constexpr int ADJ_PL = 4;    // doubles per workgroup partial of the local kernel (the first of ADJ_PA)
 constexpr int ADJ_PB = 2;    // doubles per workgroup partial of the gather kernel
+constexpr int ADJ_SUMS = ADJ_PA + ADJ_PB;
 constexpr int ADJ_PE = 9;    // doubles of an event partial (stride PART per workgroup)
 constexpr int ADJ_PC = 3;    // doubles of a wetting-chain partial (stride PART per workgroup)
 
@@ -64,17 +67,14 @@ struct AdjArgs {
     double *vtb;             // box: adjoint of the wetting-layer densities [2][S^3]
     double *ubn;             // box: uncovered-node density adjoint per kept neighbour [2][S^3]
     void *nfw;               // box: NodeFwd<T> of the nodes with sphere links [S^3]
-    double *partA;           // [nlt][ADJ_PA]
-    double *partB;           // [nwg][ADJ_PB]
+    double *partA;           // [nlt][ADJ_PL]
+    double *partB;           // [nlt][ADJ_PB]
     double *partE;           // [nbw][PART] event partials
     double *partC;           // [nbw][PART] wetting-chain partials
     double *partL;           // [2 nbw][PART] link partials (same slots as partA)
-    double *partM;           // [nmw][PART] wall-mirror partials
-    int32_t nwg;             // workgroups of the gather kernel (256 threads, one node each)
-    int32_t lty, nlt;        // local kernel: tile rows (of one plane), tiles (one workgroup each)
-    int32_t desc_nx;         // nodes per x-row (host copy, for the local kernel's LDS size)
+    int32_t lty, nlt;        // local and gather kernels: tile rows (of one plane), tiles (one workgroup each)
+    int32_t desc_nx;         // nodes per x-row (host copy, for the node kernels' LDS size)
     int32_t nbw;             // workgroups of the box kernels (256 threads, one box node each)
-    int32_t nmw;             // workgroups of the wall-face kernel (256 threads, one face node each)
 };
 
 struct RecArgs {

@@ -573,10 +573,10 @@ int tape_ck_copy(lbm_ctx *c, bool save, char *ck) {
 }
 
 struct AdjLayout {
-    int nseg = 0, seg = 0, nwg = 0, nbw = 0, nmw = 0, lty = 0, nlt = 0;
+    int nseg = 0, seg = 0, nbw = 0, lty = 0, nlt = 0;
     size_t ckb = 0, recb = 0, Ab = 0;
     size_t ck = 0, rec = 0, rst = 0, A[2] = {0, 0}, Fb = 0, vt = 0, vinv = 0, vtb = 0, ubn = 0, nfw = 0,
-           partA = 0, partB = 0, partE = 0, partC = 0, partL = 0, partM = 0, adj = 0, total = 0;
+           partA = 0, partB = 0, partE = 0, partC = 0, partL = 0, adj = 0, total = 0;
 };
 
 int adj_check(lbm_ctx *c, int32_t nsteps, int32_t segment) {
@@ -599,21 +599,12 @@ AdjLayout adj_plan(lbm_ctx *c, int32_t nsteps, int32_t segment) {
     const int64_t N = c->desc[0].N;
     const size_t te = c->prec == LBM_FP64 ? 8 : 4;
     const int64_t S3 = c->L.S3tot;
-    A.nwg = (int)((N + 255) / 256);
     A.nbw = (int)((S3 + 255) / 256);
     {
         // node-kernel tiles: ty full x-rows of one plane
         const lbm_params &q = c->p[0];
         A.lty = adj_tile_rows(q);
         A.nlt = (int)((int64_t)((q.ny + A.lty - 1) / A.lty) * q.nz);
-    }
-    {
-        const lbm_params &q = c->p[0];
-        const int64_t nn[3] = {q.nx, q.ny, q.nz};
-        int64_t faces = 0;
-        for (int ax = 0; ax < 3; ax++)
-            if (q.walls & (1u << ax)) faces += 2 * nn[(ax + 1) % 3] * nn[(ax + 2) % 3];
-        A.nmw = (int)std::max<int64_t>(1, (faces + 255) / 256);
     }
     A.ckb = align_up(tape_ck_bytes(c));
     A.recb = align_up(8 * N * te);
@@ -631,12 +622,11 @@ AdjLayout adj_plan(lbm_ctx *c, int32_t nsteps, int32_t segment) {
     A.vtb = take(sizeof(double) * 2 * S3);
     A.ubn = take(sizeof(double) * 2 * S3);
     A.nfw = take(NODE_FWD_BYTES * S3);
-    A.partA = take(sizeof(double) * ADJ_PA * A.nlt);
-    A.partB = take(sizeof(double) * ADJ_PB * A.nwg);
+    A.partA = take(sizeof(double) * ADJ_PL * A.nlt);
+    A.partB = take(sizeof(double) * ADJ_PB * A.nlt);
     A.partE = take(sizeof(double) * PART * A.nbw);
     A.partC = take(sizeof(double) * PART * A.nbw);
     A.partL = take(sizeof(double) * PART * 2 * A.nbw);
-    A.partM = take(sizeof(double) * PART * A.nmw);
     A.adj = take(sizeof(AdjState));
     A.total = o;
     return A;
@@ -1377,13 +1367,10 @@ int adjoint_backward(lbm_ctx *c, double grad[5], double *J) {
     aa.partE = reinterpret_cast<double *>(w + A.partE);
     aa.partC = reinterpret_cast<double *>(w + A.partC);
     aa.partL = reinterpret_cast<double *>(w + A.partL);
-    aa.partM = reinterpret_cast<double *>(w + A.partM);
-    aa.nwg = A.nwg;
     aa.lty = A.lty;
     aa.nlt = A.nlt;
     aa.desc_nx = q.nx;
     aa.nbw = A.nbw;
-    aa.nmw = A.nmw;
     int an = 0;  // buffer holding the adjoint of the state after the step being reversed
     for (int s = A.nseg - 1; s >= 0; s--) {
         const int K = seg_len(s);
