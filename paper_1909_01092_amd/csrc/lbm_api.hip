@@ -471,6 +471,7 @@ int enqueue_step(lbm_ctx *c, bool timed, const StepScratch &sc) {
     m.tau1 = c->tau1;
     m.noise = c->noise;
     m.groups = c->groups;
+    m.stream = 2.0 * (double)c->L.pop_elems * (double)c->es > 300e6;
     if (timed && c->ev_used + 2 > c->ev.size()) {
         for (int k = 0; k < 256; k++) {
             hipEvent_t e;

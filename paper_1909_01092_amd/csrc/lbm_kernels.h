@@ -20,6 +20,7 @@ struct MainArgs {
     int32_t tau1;              // every relaxation time of every replica is 1
     int32_t groups;            // some fluid holds several spheres
     int32_t noise;             // some replica has kT > 0
+    int32_t stream;            // the populations exceed the cache before memory
 };
 
 struct LinkArgs {

@@ -262,11 +262,12 @@ __device__ __forceinline__ S buf_ld(Rsrc r, uint32_t vo, uint32_t so) {
     else return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b16(r, vo, so, 0));
 }
 typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
-template <typename S>
+// AUX 2: non-temporal
+template <typename S, int AUX = 0>
 __device__ __forceinline__ void buf_st(S v, Rsrc r, uint32_t vo, uint32_t so) {
-    if constexpr (sizeof(S) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, v), r, vo, so, 0);
-    else if constexpr (sizeof(S) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, vo, so, 0);
-    else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, vo, so, 0);
+    if constexpr (sizeof(S) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, v), r, vo, so, AUX);
+    else if constexpr (sizeof(S) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, vo, so, AUX);
+    else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, vo, so, AUX);
 }
 
 // a wave-uniform value recomputed from here on instead of being kept (the
@@ -490,6 +491,15 @@ void k_main(MainArgs a) {
     uint32_t pos = t < nin ? (uint32_t)(t % nx) | (uint32_t)(t / nx) << 16 : 0x40000000u;
     const int pr = (ty + 2) * nx;  // LDS elements per plane and component
 
+    // Non-temporal stores where the populations cannot stay in the 256 MB cache
+    // before memory (a.stream: both buffers over 300 MB) and a row's slots fill
+    // whole 64-byte lines; FP32 and FP64.  Plain and non-temporal, us: 192 ensemble
+    // channels (9.9 GB) 2437 and 2265, 64 x 64 x 256 (319 MB) 86.6 and 83.1, 128^3
+    // 160 and 152, 64 x 64 x 200 FP64 211 and 194.  Smaller ones lose the cache (64
+    // x 64 x 224, 279 MB: 77.2 and 78.9; 6 x 32 x 32 x 128, 239 MB: 63.7 and 69.4),
+    // rows of other lengths write lines in parts (60 x 60 x 900: 290 and 326), and
+    // FP16 gains nothing (192 x 192 x 1024: 1937 and 1917; 96 x 96 x 512: 323 and 328).
+    const bool stream = sizeof(S) >= 4 && a.stream && (nx * sizeof(S)) % 64 == 0;
     const bool hp = D.has_particle;
     const int nsph = GROUP ? D.n_sph : 1;
     const PullCtx<S, T> pc = pull_ctx<S, T>(a.src, D, g);
@@ -747,13 +757,17 @@ void k_main(MainArgs a) {
                 int32_t nxs = nx;
                 renew(nxs);
                 const uint32_t nxb = (uint32_t)nxs * (uint32_t)sizeof(S);
+                auto store = [&](auto aux) {
 #pragma unroll
-                for (int i = 0; i < Q; i++) {
-                    const T inv = Rel<S>::value && !TAU1 ? T(1) / (T(wgt(i)) * sc) : T(1);
-                    S v;
-                    st_dev<S, T>(&v, out[i], inv);
-                    buf_st<S>(v, drs, own, (uint32_t)slot(l, i) * nxb);
-                }
+                    for (int i = 0; i < Q; i++) {
+                        const T inv = Rel<S>::value && !TAU1 ? T(1) / (T(wgt(i)) * sc) : T(1);
+                        S v;
+                        st_dev<S, T>(&v, out[i], inv);
+                        buf_st<S, decltype(aux)::value>(v, drs, own, (uint32_t)slot(l, i) * nxb);
+                    }
+                };
+                if (stream) store(std::integral_constant<int, 2>{});
+                else store(std::integral_constant<int, 0>{});
                 // A link that leaves the box through a y- or z-face also writes its
                 // value where the receiver pulls it from: the wall ghost x + c_i,
                 // slot opp(i) (half-way bounce-back), or the periodic image of x,
