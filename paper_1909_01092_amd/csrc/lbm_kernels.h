@@ -93,6 +93,7 @@ struct FieldArgs {
     const double *vrho;
     double *scratch;           // 9 N doubles
     double *columns;           // 8 nx ny doubles, or null
+    int32_t cz;                // planes per z-chunk of the column sums
 };
 
 // dispatch on the storage precision (0 FP64, 1 FP32, 2 FP16)
