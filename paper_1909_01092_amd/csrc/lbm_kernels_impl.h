@@ -757,6 +757,12 @@ void k_main(MainArgs a) {
                 int32_t nxs = nx;
                 renew(nxs);
                 const uint32_t nxb = (uint32_t)nxs * (uint32_t)sizeof(S);
+                // the values are final here: formed inside the two branches below, FP64
+                // sums would be fused differently from one form of the kernel to another
+                if constexpr (sizeof(T) == 8) {
+#pragma unroll
+                    for (int i = 0; i < Q; i++) asm("" : "+v"(out[i]));
+                }
                 auto store = [&](auto aux) {
 #pragma unroll
                     for (int i = 0; i < Q; i++) {
