@@ -471,7 +471,10 @@ int enqueue_step(lbm_ctx *c, bool timed, const StepScratch &sc) {
     m.tau1 = c->tau1;
     m.noise = c->noise;
     m.groups = c->groups;
-    m.stream = 2.0 * (double)c->L.pop_elems * (double)c->es > 300e6;
+    // (rows of whole 128-byte lines gain from 300 MB on, of 64-byte halves later: the
+    // main kernel's comment has both sides)
+    const double both = 2.0 * (double)c->L.pop_elems * (double)c->es;
+    m.stream = both > 350e6 ? 64 : both > 300e6 ? 128 : 0;
     if (timed && c->ev_used + 2 > c->ev.size()) {
         for (int k = 0; k < 256; k++) {
             hipEvent_t e;

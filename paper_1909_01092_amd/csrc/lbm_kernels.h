@@ -20,7 +20,7 @@ struct MainArgs {
     int32_t tau1;              // every relaxation time of every replica is 1
     int32_t groups;            // some fluid holds several spheres
     int32_t noise;             // some replica has kT > 0
-    int32_t stream;            // the populations exceed the cache before memory
+    int32_t stream;            // store rows of a multiple of this many bytes (64, 128) past the caches; 0: none
 };
 
 struct LinkArgs {

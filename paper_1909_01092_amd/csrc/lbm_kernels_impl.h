@@ -492,14 +492,16 @@ void k_main(MainArgs a) {
     const int pr = (ty + 2) * nx;  // LDS elements per plane and component
 
     // Non-temporal stores where the populations cannot stay in the 256 MB cache
-    // before memory (a.stream: both buffers over 300 MB) and a row's slots fill
-    // whole 64-byte lines; FP32 and FP64.  Plain and non-temporal, us: 192 ensemble
-    // channels (9.9 GB) 2437 and 2265, 64 x 64 x 256 (319 MB) 86.6 and 83.1, 128^3
-    // 160 and 152, 64 x 64 x 200 FP64 211 and 194.  Smaller ones lose the cache (64
-    // x 64 x 224, 279 MB: 77.2 and 78.9; 6 x 32 x 32 x 128, 239 MB: 63.7 and 69.4),
-    // rows of other lengths write lines in parts (60 x 60 x 900: 290 and 326), and
-    // FP16 gains nothing (192 x 192 x 1024: 1937 and 1917; 96 x 96 x 512: 323 and 328).
-    const bool stream = sizeof(S) >= 4 && a.stream && (nx * sizeof(S)) % 64 == 0;
+    // before memory (both buffers over 300 MB where a row's slots fill whole 128-byte
+    // lines, over 350 MB where they fill 64-byte halves); FP32 and FP64.  Plain and
+    // non-temporal, us: 192 ensemble channels (9.9 GB) 2437 and 2265, 64 x 64 x 256
+    // (319 MB) 86.6 and 83.1, 128^3 160 and 152, 64 x 64 x 200 FP64 211 and 194;
+    // halves: 9 x 48^3 (328 MB) 85.2 and 88.1, 3 x 48 x 48 x 192 (430 MB) 124.4 and
+    // 120.6.  Smaller ones lose the cache (64 x 64 x 224, 279 MB: 77.2 and 78.9; 6 x
+    // 32 x 32 x 128, 239 MB: 63.7 and 69.4), rows of other lengths write lines in
+    // parts (60 x 60 x 900: 290 and 326), and FP16 gains nothing (192 x 192 x 1024:
+    // 1937 and 1917; 96 x 96 x 512: 323 and 328).
+    const bool stream = sizeof(S) >= 4 && a.stream && ((nx * (int)sizeof(S)) & (a.stream - 1)) == 0;
     const bool hp = D.has_particle;
     const int nsph = GROUP ? D.n_sph : 1;
     const PullCtx<S, T> pc = pull_ctx<S, T>(a.src, D, g);
