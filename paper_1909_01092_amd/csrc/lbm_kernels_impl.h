@@ -601,7 +601,7 @@ void k_main(MainArgs a) {
     // node are loaded while the current plane collides (38 registers, which the
     // packed position leaves room for at four waves per SIMD), so that memory is
     // busy in the collision phase too.  Measured without and with: 60 x 60 x 900
-    // 296 -> 290 us, 192 ensemble channels 2464 -> 2400, 8 x (32 x 32 x 128) 61.1 ->
+    // 296 -> 290 us, 192 ensemble channels 2464 -> 2400, 6 x (32 x 32 x 128) 61.1 ->
     // 58.8, 64 x 64 x 256 86.7 -> 85.4.  FP16 storage loses by it (192 x 192 x 1024:
     // 1912 -> 2082 us; bound by the vector ALU, and each 16-bit number held takes a
     // register), and the general and FP64 forms have no registers left.
@@ -906,10 +906,10 @@ __device__ __forceinline__ T store_round(double v, T inv_scale, T scale, S &sv) 
 // each, in code that is the same for every direction (the velocities come from
 // bit tables) and a fifth as long.  With one lane per node every surface wave
 // issued 1.7 k (k_links) and 2.2 k (k_particle) vector instructions.
-// 64 x 64 x 256 channel (R = 8): k_links 12.6 -> 6.8 us, k_particle 23.3 -> 16 us;
+// 64 x 64 x 256 channel (R = 8): k_links 12.6 -> 6.5 us, k_particle 23.3 -> 11.6;
 // 16 x 16 x 32 (R = 3): 11.7 -> 5.7 and 16.8 -> 10.7 us.  192 spheres, where the
-// chip is full and the quads' common work counts: both together 145 -> 175 us of
-// a 2.7 ms step.
+// chip is full and the quads' common work counts: both together 145 -> 176 us of
+// a 2.4 ms step.
 constexpr int QM = 5;
 constexpr uint32_t dir_bits(int ax, int m) {  // c + 1 of the four directions 5 q + m, two bits each
     uint32_t v = 0;
