@@ -275,9 +275,9 @@ __device__ __forceinline__ void buf_st(S v, Rsrc r, uint32_t vo, uint32_t so) {
 __device__ __forceinline__ void renew(int32_t &v) { asm volatile("" : "+s"(v)); }
 
 // Components L0 .. L0 + NL - 1 of a node; z uniform over the wave, (x, y) per
-// lane.  As numbers T, or unscaled as they are stored (FP16, S = E).
-template <int NL, typename E, typename S, typename T>
-__device__ __forceinline__ void pull_row(PullCtx<S, T> c, int x, int y, int z, int L0, E (&d)[NL][Q]) {
+// lane.
+template <int NL, typename S, typename T>
+__device__ __forceinline__ void pull_row(PullCtx<S, T> c, int x, int y, int z, int L0, T (&d)[NL][Q]) {
     constexpr uint32_t es = sizeof(S);
     renew(c.nx);
     renew(c.RS);
@@ -306,8 +306,7 @@ __device__ __forceinline__ void pull_row(PullCtx<S, T> c, int x, int y, int z, i
 #pragma unroll
         for (int l = 0; l < NL; l++) {
             const S v = buf_ld<S>(cz(i) > 0 ? r1 : r0, vo, so + (uint32_t)(l * SLOTS.n[i]) * nxb);
-            if constexpr (Rel<S>::value && sizeof(E) == sizeof(S)) d[l][i] = v;
-            else d[l][i] = ld_dev<S, T>(&v, w * (L0 + l ? c.scale[1] : c.scale[0]));
+            d[l][i] = ld_dev<S, T>(&v, w * (L0 + l ? c.scale[1] : c.scale[0]));
         }
     }
 }
@@ -348,28 +347,6 @@ __device__ __forceinline__ void node_moments(const T (&d)[2][Q], NodeM<T> &s) {
             if (cz(i) > 0) jz += d[l][i]; else if (cz(i) < 0) jz -= d[l][i];
         }
         s.rd[l] = r; s.j[l][0] = jx; s.j[l][1] = jy; s.j[l][2] = jz;
-    }
-}
-
-// The same from relative deviations h = d / (w_i rho0_l): each sum takes the
-// weight in its multiply-add, which reads the 16-bit value as it is stored (49
-// operations per component against 87 with a conversion and a product first).
-template <typename T>
-__device__ __forceinline__ void node_moments_rel(const T (&h)[2][Q], const T (&rho0)[2], NodeM<T> &s) {
-#pragma unroll
-    for (int l = 0; l < 2; l++) {
-        T r = T(0), j[3] = {T(0), T(0), T(0)};
-#pragma unroll
-        for (int i = 0; i < Q; i++) {
-            const T w = T(wgt(i));
-            r = fma(h[l][i], w, r);
-            if (cx(i)) j[0] = fma(h[l][i], cx(i) > 0 ? w : -w, j[0]);
-            if (cy(i)) j[1] = fma(h[l][i], cy(i) > 0 ? w : -w, j[1]);
-            if (cz(i)) j[2] = fma(h[l][i], cz(i) > 0 ? w : -w, j[2]);
-        }
-        s.rd[l] = r * rho0[l];
-#pragma unroll
-        for (int q = 0; q < 3; q++) s.j[l][q] = j[q] * rho0[l];
     }
 }
 
@@ -540,7 +517,7 @@ void k_main(MainArgs a) {
     // density deviation of a box node: pulled (plus the mass correction), or
     // the wetting-layer value on particle nodes; fluid nodes also return
     // their moments (have: the node's populations, if they are loaded already)
-    auto node_density = [&](int xx, int yy, int zz, bool zbox, const S(*have)[Q], NodeM<T> &s, T &rA, T &rB) -> bool {
+    auto node_density = [&](int xx, int yy, int zz, bool zbox, const T(*have)[Q], NodeM<T> &s, T &rA, T &rB) -> bool {
         int b = -1;
         if (zbox) b = bbox_index(xx, yy, zz, org, Sx, g);
         if (b < 0 || !(pmask[b] & MASK_SOLID)) {
@@ -564,15 +541,13 @@ void k_main(MainArgs a) {
             if (vi < 0) {
                 T d[2][Q];
                 if constexpr (TAU1) {
-                    S raw[2][Q];
-                    if (!have) pull_row<2>(pcl, xx, yy, zz, 0, raw);
+                    if (!have) pull_row<2>(pcl, xx, yy, zz, 0, d);
 #pragma unroll
-                    for (int i = 0; i < Q; i++) {
-                        d[0][i] = T(have ? have[0][i] : raw[0][i]);
-                        d[1][i] = T(have ? have[1][i] : raw[1][i]);
+                    for (int i = 0; i < Q && have; i++) {
+                        d[0][i] = have[0][i];
+                        d[1][i] = have[1][i];
                     }
-                    if constexpr (Rel<S>::value) node_moments_rel(d, pcl.scale, s);
-                    else node_moments(d, s);
+                    node_moments(d, s);
                 } else {
                     pull_row<2>(pcl, xx, yy, zz, 0, d);
                     T unused[Q];
@@ -606,7 +581,7 @@ void k_main(MainArgs a) {
     // 1912 -> 2082 us; bound by the vector ALU, and each 16-bit number held takes a
     // register), and the general and FP64 forms have no registers left.
     constexpr bool PREF = main_fast_form<S, T, TAU1> && sizeof(S) == 4;
-    S pre[2][Q];
+    T pre[2][Q];
     auto prefetch = [&](int zp) {
         const int zz = mirror1(zp, g.nz, g.wz);
         const int x = (int)(pos & 0xffffu), yl = (int)(pos >> 16);
@@ -744,8 +719,7 @@ void k_main(MainArgs a) {
                 }
                 T out[Q];
                 if constexpr (TAU1) {
-                    if constexpr (Rel<S>::value) relax_tau1_rel(r0l, sig, rdl, jl, Fl, u, xid, zl, cf, out);
-                    else relax_tau1(r0l, sig, rdl, jl, Fl, u, xid, zl, cf, out);
+                    relax_tau1(r0l, sig, rdl, jl, Fl, u, xid, zl, cf, out);
                 } else {
                     T ml[Q], rdm, jm[3];
                     component_modes(dl1[0], rdm, jm, ml);
@@ -768,7 +742,7 @@ void k_main(MainArgs a) {
                 auto store = [&](auto aux) {
 #pragma unroll
                     for (int i = 0; i < Q; i++) {
-                        const T inv = Rel<S>::value && !TAU1 ? T(1) / (T(wgt(i)) * sc) : T(1);
+                        const T inv = Rel<S>::value ? T(1) / (T(wgt(i)) * sc) : T(1);
                         S v;
                         st_dev<S, T>(&v, out[i], inv);
                         buf_st<S, decltype(aux)::value>(v, drs, own, (uint32_t)slot(l, i) * nxb);
@@ -786,7 +760,7 @@ void k_main(MainArgs a) {
 #pragma unroll
                     for (int i = 1; i < Q; i++) {
                         if (cy(i) == 0 && cz(i) == 0) continue;
-                        const T inv = Rel<S>::value && !TAU1 ? T(1) / (T(wgt(i)) * sc) : T(1);
+                        const T inv = Rel<S>::value ? T(1) / (T(wgt(i)) * sc) : T(1);
                         const bool ex = cx(i) > 0 ? xhi : (cx(i) < 0 ? xlo : false);
                         const bool ey = cy(i) > 0 ? yhi : (cy(i) < 0 ? ylo : false);
                         const bool ez = cz(i) > 0 ? zhi : (cz(i) < 0 ? zlo : false);

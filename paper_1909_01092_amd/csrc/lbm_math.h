@@ -226,10 +226,10 @@ __host__ __device__ inline void component_modes(const T (&f)[Q], T &rd, T (&j)[3
     m[18] = -sy + sz + Exy - Exz;
 }
 
-// f_i = w_i sum_k e_k(c_i) a_k with a_k = m_k / b_k; OVER_W: f_i / w_i.
-template <bool OVER_W = false, typename T>
+// f_i = w_i sum_k e_k(c_i) a_k with a_k = m_k / b_k.
+template <typename T>
 __host__ __device__ inline void back_transform(const T (&a)[Q], T (&f)[Q]) {
-    const T w0 = T(OVER_W ? 1.0 : 1.0 / 3.0), w1 = T(OVER_W ? 1.0 : 1.0 / 18.0), w2 = T(OVER_W ? 1.0 : 1.0 / 36.0);
+    const T w0 = T(1.0 / 3.0), w1 = T(1.0 / 18.0), w2 = T(1.0 / 36.0);
     f[0] = w0 * (a[0] - a[4] + a[16]);
     const T Ex = w1 * (a[0] + T(2) * a[5] - T(2) * a[16] - T(2) * a[17]);
     const T Ox = w1 * (a[1] - T(2) * a[10]);
@@ -342,42 +342,6 @@ __host__ __device__ inline void relax_tau1(T rho0l, T sig, T rd, const T (&j)[3]
 #pragma unroll
     for (int k = 10; k < Q; k++) a[k] = T(inv_norm(k) * sqrt_norm(k)) * ng * zl[k - 4];
     back_transform(a, out);
-}
-
-// The same as relative deviations f_i / (w_i rho0_l), every input that a mode is
-// linear in being scaled by 1 / rho0_l first (9 products in place of the 38 of
-// scaling by 1 / (w_i rho0_l) and the 19 by w_i).
-template <typename T>
-__host__ __device__ inline void relax_tau1_rel(T rho0l, T sig, T rd, const T (&j)[3], const T (&F_in)[3],
-                                               const T (&u)[3], const T (&xid_in)[3], const T (&zl)[16],
-                                               const Coef<T> &c, T (&out)[Q]) {
-    const T inv = T(1) / rho0l;
-    T r = rho0l + rd;
-    const T sq = (c.noise ? sqrt(tmax0(r)) : T(0)) * inv;
-    const T nb = c.nb * sq, ns = c.ns * sq, ng = c.ng * sq;
-    r *= inv;
-    rd *= inv;
-    const T Fl[3] = {F_in[0] * inv, F_in[1] * inv, F_in[2] * inv};
-    const T xid[3] = {xid_in[0] * inv, xid_in[1] * inv, xid_in[2] * inv};
-    const T uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-    T a[Q];
-    a[0] = rd;
-    for (int q = 0; q < 3; q++) a[1 + q] = T(3) * (r * u[q] + T(0.5) * Fl[q] + sig * xid[q]);
-    const T uF = u[0] * Fl[0] + u[1] * Fl[1] + u[2] * Fl[2];
-    const T e4 = r * uu, e5 = r * (T(3) * u[0] * u[0] - uu), e6 = r * (u[1] * u[1] - u[2] * u[2]);
-    const T e7 = r * u[0] * u[1], e8 = r * u[1] * u[2], e9 = r * u[0] * u[2];
-    const T f4 = uF, f5 = T(3) * u[0] * Fl[0] - uF, f6 = u[1] * Fl[1] - u[2] * Fl[2];
-    const T f7 = T(0.5) * (u[0] * Fl[1] + u[1] * Fl[0]), f8 = T(0.5) * (u[1] * Fl[2] + u[2] * Fl[1]);
-    const T f9 = T(0.5) * (u[0] * Fl[2] + u[2] * Fl[0]);
-    a[4] = T(inv_norm(4)) * (e4 + f4) + T(inv_norm(4) * sqrt_norm(4)) * nb * zl[0];
-    a[5] = T(inv_norm(5)) * (e5 + f5) + T(inv_norm(5) * sqrt_norm(5)) * ns * zl[1];
-    a[6] = T(inv_norm(6)) * (e6 + f6) + T(inv_norm(6) * sqrt_norm(6)) * ns * zl[2];
-    a[7] = T(inv_norm(7)) * (e7 + f7) + T(inv_norm(7) * sqrt_norm(7)) * ns * zl[3];
-    a[8] = T(inv_norm(8)) * (e8 + f8) + T(inv_norm(8) * sqrt_norm(8)) * ns * zl[4];
-    a[9] = T(inv_norm(9)) * (e9 + f9) + T(inv_norm(9) * sqrt_norm(9)) * ns * zl[5];
-#pragma unroll
-    for (int k = 10; k < Q; k++) a[k] = T(inv_norm(k) * sqrt_norm(k)) * ng * zl[k - 4];
-    back_transform<true>(a, out);
 }
 
 }  // namespace lbm
