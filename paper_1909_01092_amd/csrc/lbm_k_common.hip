@@ -104,18 +104,14 @@ __global__ __launch_bounds__(256) void k_fields_b(FieldArgs a) {
 
 // Column sums over z: mass_A, mass_B, j (3), sum |u|^2, sum u_z, fluid count.
 // One thread per column (x, y) and z-chunk of a.cz planes, marching over its
-// planes: what a plane's 3 x 3 neighbourhood gives to the force of the planes
-// below, at and above it is formed once, so 9 densities per component are read
-// per node and not 18, and the velocity (as in k_fields_b) stays in registers.
-// Partial sums per chunk go where k_fields_b would write the velocity; k_columns
-// adds them in the order of the chunks.  Bound by memory: 192 x 192 x 1024 takes
-// 0.60 ms with k_columns, where k_fields_b and one thread per whole column took
-// 2.24 (60 x 60 x 900, 15 workgroups before: 88 us and 730).
-struct PlaneTerms {
-    double x0, y0;     // to the x and y gradients of the plane itself
-    double x1, y1, z1; // to those of the planes next to it (z: added below, subtracted above)
-};
-
+// planes with the 3 x 3 neighbourhoods of three of them in registers, so 9
+// densities per component are read per node and not 18, and the velocity (formed
+// as k_fields_b forms it, term by term: at rest it is rounding error of the
+// gradient) stays in registers.  Partial sums per chunk go where k_fields_b would
+// write the velocity; k_columns adds them in the order of the chunks.  Bound by
+// memory: 192 x 192 x 1024 takes 0.61 ms with k_columns, where k_fields_b and one
+// thread per whole column took 2.24 (60 x 60 x 900, 15 workgroups before: 89 us
+// and 730).
 __global__ __launch_bounds__(256) void k_column_parts(FieldArgs a) {
     const RepDesc &D = a.desc[a.rep];
     const Geo g = geo_of(D);
@@ -127,63 +123,53 @@ __global__ __launch_bounds__(256) void k_column_parts(FieldArgs a) {
     const int64_t ys[3] = {(int64_t)mirror1(y - 1, g.ny, g.wy) * g.nx, (int64_t)y * g.nx,
                            (int64_t)mirror1(y + 1, g.ny, g.wy) * g.nx};
     const double *rt = a.scratch, *jt = a.scratch + 2 * N, *sol = a.scratch + 8 * N;
-    const double w1 = wgt(1), w2 = wgt(7), G = D.G;
-    const double af[3] = {D.af[0], D.af[1], D.af[2]};
-    double r0[2];  // densities of the column itself
-    auto terms = [&](int zp, int l) {
-        const double *r = rt + l * N + plane * mirror1(zp, g.nz, g.wz);
-        double v[3][3];
+    double v[3][2][9];  // planes z - 1, z, z + 1; component; 3 x 3 neighbourhood
+    auto load = [&](int zp, double(&to)[2][9]) {
+        const double *r = rt + plane * mirror1(zp, g.nz, g.wz);
 #pragma unroll
-        for (int j = 0; j < 3; j++)
+        for (int l = 0; l < 2; l++)
 #pragma unroll
-            for (int i = 0; i < 3; i++) v[j][i] = r[ys[j] + xs[i]];
-        r0[l] = v[1][1];
-        PlaneTerms t;
-        const double dx = v[1][2] - v[1][0], dy = v[2][1] - v[0][1];
-        const double da = v[2][2] - v[0][0], db = v[0][2] - v[2][0];
-        t.x0 = w1 * dx + w2 * (da + db);
-        t.y0 = w1 * dy + w2 * (da - db);
-        t.x1 = w2 * dx;
-        t.y1 = w2 * dy;
-        t.z1 = w1 * v[1][1] + w2 * ((v[1][2] + v[1][0]) + (v[2][1] + v[0][1]));
-        return t;
+            for (int k = 0; k < 9; k++) to[l][k] = r[l * N + ys[k / 3] + xs[k % 3]];
     };
     const int z0 = blockIdx.y * a.cz, z1 = min(z0 + a.cz, g.nz);
-    PlaneTerms lo[2], at[2], hi[2];
-    double ra[2];
-    for (int l = 0; l < 2; l++) lo[l] = terms(z0 - 1, l);
-    for (int l = 0; l < 2; l++) at[l] = terms(z0, l);
-    ra[0] = r0[0];
-    ra[1] = r0[1];
+    load(z0 - 1, v[0]);
+    load(z0, v[1]);
     double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int z = z0; z < z1; z++) {
-        for (int l = 0; l < 2; l++) hi[l] = terms(z + 1, l);
+        load(z + 1, v[2]);
         const int64_t n = c + plane * z;
         const double j[3] = {jt[n], jt[N + n], jt[2 * N + n]};
         if (sol[n] == 0.0) {
+            double grad[2][3] = {{0, 0, 0}, {0, 0, 0}};
+#pragma unroll
+            for (int i = 1; i < Q; i++)
+#pragma unroll
+                for (int l = 0; l < 2; l++) {
+                    const double t = wgt(i) * v[cz(i) + 1][l][3 * (cy(i) + 1) + cx(i) + 1];
+                    grad[l][0] += t * cx(i); grad[l][1] += t * cy(i); grad[l][2] += t * cz(i);
+                }
+            const double rA = v[1][0][4], rB = v[1][1][4];
             double u[3];
 #pragma unroll
             for (int q = 0; q < 3; q++) {
-                double gr[2];
-                for (int l = 0; l < 2; l++)
-                    gr[l] = q == 0 ? at[l].x0 + (lo[l].x1 + hi[l].x1)
-                          : q == 1 ? at[l].y0 + (lo[l].y1 + hi[l].y1) : hi[l].z1 - lo[l].z1;
-                const double FA = -G * ra[0] * gr[1] + ra[0] * af[q];
-                const double FB = -G * ra[1] * gr[0] + ra[1] * af[q];
-                u[q] = (j[q] + 0.5 * (FA + FB)) / (ra[0] + ra[1]);
+                const double FA = -D.G * rA * grad[1][q] + rA * D.af[q];
+                const double FB = -D.G * rB * grad[0][q] + rB * D.af[q];
+                u[q] = (j[q] + 0.5 * (FA + FB)) / (rA + rB);
                 s[2 + q] += j[q];
             }
-            s[0] += ra[0];
-            s[1] += ra[1];
+            s[0] += rA;
+            s[1] += rB;
             s[5] += u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
             s[6] += u[2];
             s[7] += 1.0;
         }
-        for (int l = 0; l < 2; l++) {
-            lo[l] = at[l];
-            at[l] = hi[l];
-            ra[l] = r0[l];
-        }
+#pragma unroll
+        for (int l = 0; l < 2; l++)
+#pragma unroll
+            for (int k = 0; k < 9; k++) {
+                v[0][l][k] = v[1][l][k];
+                v[1][l][k] = v[2][l][k];
+            }
     }
     double *part = gridDim.y == 1 ? a.columns : a.scratch + 5 * N + (int64_t)blockIdx.y * 8 * plane;
     for (int k = 0; k < 8; k++) part[k * plane + c] = s[k];
