@@ -96,6 +96,14 @@ constexpr int PART = 24;     // doubles per workgroup partial
 constexpr int RAW = 5;       // doubles per box node: rho_A, rho_B, j (post-streaming, step n+1)
 constexpr int MAX_GROUP = 16;  // spheres per fluid
 
+// First coordinate of the bounding box of a sphere whose lowest point lies at v,
+// two nodes before it; held within +-2^28, where differences of two origins and
+// an origin plus a box coordinate still are whole 32-bit numbers (a diverging
+// sphere reaches any v; not a number counts as the lower end).
+__host__ __device__ inline int32_t box_start(double v) {
+    return (int32_t)fmin(fmax(floor(v), -0x1p28), 0x1p28) - 2;
+}
+
 // Whether the boxes of edge Sa at oa and of edge Sb at ob share a node: per
 // axis, half-open intervals on a ring of n nodes (periodic axes, n >= Sa, Sb)
 // or on a line (walled axes); they share a node when they meet on all three.
