@@ -311,6 +311,19 @@ __device__ __forceinline__ void pull_row(PullCtx<S, T> c, int x, int y, int z, i
     }
 }
 
+// FP16 storage: a pulled population is a product (number times scale), which the
+// compiler may round, or fuse into the sums it enters.  Of two opposite ones the
+// second (even i) is rounded here, so that component_modes always fuses the first,
+// whichever of its outputs are read: a node's density must not depend on whether
+// it is a tile's own node or a neighbour tile's halo.
+template <typename S, typename T>
+__device__ __forceinline__ void settle_pairs(T (&d)[Q]) {
+    if constexpr (Rel<S>::value) {
+#pragma unroll
+        for (int i = 2; i < Q; i += 2) asm("" : "+v"(d[i]));
+    }
+}
+
 // any node
 template <typename S, typename T>
 __device__ __forceinline__ void pull_node(const PullCtx<S, T> &c, int x, int y, int z, T (&d)[2][Q]) {
@@ -550,6 +563,8 @@ void k_main(MainArgs a) {
                     node_moments(d, s);
                 } else {
                     pull_row<2>(pcl, xx, yy, zz, 0, d);
+                    settle_pairs<S>(d[0]);
+                    settle_pairs<S>(d[1]);
                     T unused[Q];
                     component_modes(d[0], s.rd[0], s.j[0], unused);
                     component_modes(d[1], s.rd[1], s.j[1], unused);
@@ -677,8 +692,13 @@ void k_main(MainArgs a) {
             T F[2][3];
 #pragma unroll
             for (int q = 0; q < 3; q++) {
-                F[0][q] = -G * rl[0] * grad[1][q] + rl[0] * af[q];
-                F[1][q] = -G * rl[1] * grad[0][q] + rl[1] * af[q];
+                if constexpr (TAU1) {  // (rounded as the compiler takes it; below: stated)
+                    F[0][q] = -G * rl[0] * grad[1][q] + rl[0] * af[q];
+                    F[1][q] = -G * rl[1] * grad[0][q] + rl[1] * af[q];
+                } else {
+                    F[0][q] = fma_of(-G * rl[0], grad[1][q], rl[0] * af[q]);
+                    F[1][q] = fma_of(-G * rl[1], grad[0][q], rl[1] * af[q]);
+                }
             }
             const uint32_t node = (uint32_t)(x + nx * (y + g.ny * z));
             T u[3], xid[3];
@@ -722,6 +742,7 @@ void k_main(MainArgs a) {
                     relax_tau1(r0l, sig, rdl, jl, Fl, u, xid, zl, cf, out);
                 } else {
                     T ml[Q], rdm, jm[3];
+                    settle_pairs<S>(dl1[0]);
                     component_modes(dl1[0], rdm, jm, ml);
                     // each mode a number of its own: fused into the relaxation the
                     // sums would round differently from form to form

@@ -193,6 +193,10 @@ __host__ __device__ inline float recip(float a) {
 #endif
 }
 
+// a b + c, rounded once
+__host__ __device__ inline double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__host__ __device__ inline float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
 // Density deviation, momentum and modes 4..18 of one component (orthogonal
 // polynomial basis; modes of the deviation from w_i rho0 equal those of f for
 // k >= 1).
@@ -279,6 +283,9 @@ __host__ __device__ inline void common_velocity(const T (&rd)[2], const T (&j)[2
 //   m*_k = m_eq + g_k (m_k - m_eq) + (1 + g_k)/2 Phi_k + noise,   k = 4..9
 //   m*_k = g_g m_k + noise,                                         k = 10..18
 // noise amplitude sqrt(mu rho_l b_k (1 - g_k^2)), mu = kT / c_s^2.
+// The noise is fused onto the relaxed mode, which is rounded first: which of the
+// two products a compiler fuses differs from one form of a kernel to the next, and
+// 16-bit storage turns the last bit of FP32 into its own.
 template <typename T>
 __host__ __device__ inline void relax_component(T rho0l, T sig, T rd, const T (&j)[3],
                                                 const T (&m)[Q], const T (&Fl)[3], const T (&u)[3],
@@ -302,15 +309,15 @@ __host__ __device__ inline void relax_component(T rho0l, T sig, T rd, const T (&
     const T f6 = T(2) * (u[1] * Fl[1] - u[2] * Fl[2]);
     const T f7 = u[0] * Fl[1] + u[1] * Fl[0], f8 = u[1] * Fl[2] + u[2] * Fl[1];
     const T f9 = u[0] * Fl[2] + u[2] * Fl[0];
-    a[4] = T(inv_norm(4)) * (e4 + c.gb * (m[4] - e4) + hb * f4) + T(inv_norm(4) * sqrt_norm(4)) * nb * zl[0];
-    a[5] = T(inv_norm(5)) * (e5 + c.gs * (m[5] - e5) + hs * f5) + T(inv_norm(5) * sqrt_norm(5)) * ns * zl[1];
-    a[6] = T(inv_norm(6)) * (e6 + c.gs * (m[6] - e6) + hs * f6) + T(inv_norm(6) * sqrt_norm(6)) * ns * zl[2];
-    a[7] = T(inv_norm(7)) * (e7 + c.gs * (m[7] - e7) + hs * f7) + T(inv_norm(7) * sqrt_norm(7)) * ns * zl[3];
-    a[8] = T(inv_norm(8)) * (e8 + c.gs * (m[8] - e8) + hs * f8) + T(inv_norm(8) * sqrt_norm(8)) * ns * zl[4];
-    a[9] = T(inv_norm(9)) * (e9 + c.gs * (m[9] - e9) + hs * f9) + T(inv_norm(9) * sqrt_norm(9)) * ns * zl[5];
+    a[4] = fma_of(T(inv_norm(4) * sqrt_norm(4)) * nb, zl[0], T(inv_norm(4)) * (e4 + c.gb * (m[4] - e4) + hb * f4));
+    a[5] = fma_of(T(inv_norm(5) * sqrt_norm(5)) * ns, zl[1], T(inv_norm(5)) * (e5 + c.gs * (m[5] - e5) + hs * f5));
+    a[6] = fma_of(T(inv_norm(6) * sqrt_norm(6)) * ns, zl[2], T(inv_norm(6)) * (e6 + c.gs * (m[6] - e6) + hs * f6));
+    a[7] = fma_of(T(inv_norm(7) * sqrt_norm(7)) * ns, zl[3], T(inv_norm(7)) * (e7 + c.gs * (m[7] - e7) + hs * f7));
+    a[8] = fma_of(T(inv_norm(8) * sqrt_norm(8)) * ns, zl[4], T(inv_norm(8)) * (e8 + c.gs * (m[8] - e8) + hs * f8));
+    a[9] = fma_of(T(inv_norm(9) * sqrt_norm(9)) * ns, zl[5], T(inv_norm(9)) * (e9 + c.gs * (m[9] - e9) + hs * f9));
 #pragma unroll
     for (int k = 10; k < Q; k++)
-        a[k] = T(inv_norm(k)) * c.gg * m[k] + T(inv_norm(k) * sqrt_norm(k)) * ng * zl[k - 4];
+        a[k] = fma_of(T(inv_norm(k) * sqrt_norm(k)) * ng, zl[k - 4], T(inv_norm(k)) * c.gg * m[k]);
     back_transform(a, out);
 }
 
