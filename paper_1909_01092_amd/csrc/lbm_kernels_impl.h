@@ -1006,22 +1006,11 @@ __device__ __forceinline__ double chain_sum(const double (&v)[QM]) {
     return quad_bcast<3>(x);
 }
 
-// Origin of a box, brought within one period of the lattice on its periodic axes
-// (a diverging sphere may pass many periods in a step, and the steps queued
-// behind that one still run); on a walled axis kept.  Uniform over the workgroup,
-// so in every ordinary step this is a comparison.
-__host__ __device__ __forceinline__ void box_origin(const int32_t *org, const Geo &g, int32_t (&at)[3]) {
-    at[0] = !g.wx && (org[0] <= -g.nx || org[0] >= g.nx) ? org[0] % g.nx : org[0];
-    at[1] = !g.wy && (org[1] <= -g.ny || org[1] >= g.ny) ? org[1] % g.ny : org[1];
-    at[2] = !g.wz && (org[2] <= -g.nz || org[2] >= g.nz) ? org[2] % g.nz : org[2];
-}
-
-// Box node b of the box at org (edge S; box_origin gave org): its box coordinates
-// and lattice position; false beyond the box or in a wall layer.  The box starts
-// less than one period before or after the lattice's first node and is no longer
-// than one, so one period brings every position into the lattice.
-__host__ __device__ __forceinline__ bool box_node(int b, const int32_t (&org)[3], int S, const Geo &g, int (&bb)[3],
-                                                  int (&p)[3]) {
+// Box node b of the box at org (edge S): its box coordinates and lattice
+// position; false beyond the box, in a wall layer, or more than a period away: a
+// diverging sphere may pass several periods in a step, and the steps queued behind
+// that one still run (they find no node of it).
+__host__ __device__ __forceinline__ bool box_node(int b, const int32_t *org, int S, const Geo &g, int (&bb)[3], int (&p)[3]) {
     const uint32_t ub = (uint32_t)b, uS = (uint32_t)S;
     const uint32_t row = ub / uS;
     bb[0] = (int)(ub - row * uS);
@@ -1033,10 +1022,8 @@ __host__ __device__ __forceinline__ bool box_node(int b, const int32_t (&org)[3]
 #pragma unroll
     for (int a = 0; a < 3; a++) {
         int v = (int)((uint32_t)org[a] + (uint32_t)bb[a]);
-        if (v < 0 || v >= n3[a]) {
-            if (w3[a]) in = false;
-            else v = v < 0 ? v + n3[a] : v - n3[a];
-        }
+        if (!w3[a]) v = v < 0 ? v + n3[a] : (v >= n3[a] ? v - n3[a] : v);
+        in = in && (uint32_t)v < (uint32_t)n3[a];
         p[a] = v;
     }
     return in;
@@ -1112,9 +1099,7 @@ __global__ __launch_bounds__(K3_THREADS) void k_links(LinkArgs a) {
     const int t = threadIdx.x, q = t & 3;
     const int local = blockIdx.x - D.k3_begin;
     const int Sx = D.S, S3 = Sx * Sx * Sx;
-    const int32_t raw_org[3] = {st.org[0], st.org[1], st.org[2]};
-    int32_t org[3];
-    box_origin(raw_org, g, org);
+    const int32_t org[3] = {st.org[0], st.org[1], st.org[2]};
     const double X[3] = {st.X[0], st.X[1], st.X[2]}, U[3] = {st.U[0], st.U[1], st.U[2]};
     const double W[3] = {st.W[0], st.W[1], st.W[2]};
     const double dlt[2] = {st.delta[0], st.delta[1]};
@@ -1560,17 +1545,14 @@ __global__ __launch_bounds__(K3_THREADS) void k_particle(ParticleArgs a) {
         return;
     }
     const Geo g = geo_of(D);
-    const int32_t raw_old[3] = {st->org[0], st->org[1], st->org[2]};
-    int32_t orgo[3];
-    box_origin(raw_old, g, orgo);
+    const int32_t orgo[3] = {st->org[0], st->org[1], st->org[2]};
     const Axis ax = axis_of(D, st, t);
     // 1. link momentum exchange and wetting-layer reaction of step n
     link_sums(a.part1 + D.part3_off, D.k3_count, sh, t);
     // 2. Newton-Euler, leap-frog
     newton_euler(D, ax, g, sh, t);
     const double Xn[3] = {sh.mo.Xn[0], sh.mo.Xn[1], sh.mo.Xn[2]};
-    int32_t org[3];
-    box_origin(sh.mo.org, g, org);
+    const int org[3] = {sh.mo.org[0], sh.mo.org[1], sh.mo.org[2]};
     const int Sx = D.S, S3 = Sx * Sx * Sx;
     const double *raw = a.raw + D.bbox_off * RAW;
     double *vrho = a.vrho + D.bbox_off * 2;

@@ -1,7 +1,8 @@
 // Host run of the sphere-box coordinates (lbm_kernels_impl.h): for origins over
 // the whole int32 range, every wall mask and boxes as long as the lattice down to
 // the smallest, every node that box_node accepts lies inside the lattice, on
-// the coordinate that a 64-bit remainder gives.  Prints the number of nodes
+// the coordinate that a 64-bit remainder gives, and every such node of a box that
+// starts within one period of the lattice is accepted.  Prints the number of nodes
 // checked; returns 1 at the first one that does not.
 #include <climits>
 #include <cstdio>
@@ -25,17 +26,15 @@ int main() {
                     const int S = s[3], n3[3] = {g.nx, g.ny, g.nz};
                     int32_t org[3] = {1, -2, 3};
                     org[ax] = f;
-                    int32_t at[3];
-                    box_origin(org, g, at);
                     for (int b = 0; b < S * S * S; b++) {
                         int bb[3], p[3];
-                        const bool in = box_node(b, at, S, g, bb, p);
+                        const bool in = box_node(b, org, S, g, bb, p);
                         for (int a = 0; a < 3; a++) {
                             const bool wall = walls & (1u << a);
                             const int64_t raw = (int64_t)org[a] + bb[a];
                             const int64_t want = wall ? raw : (raw % n3[a] + n3[a]) % n3[a];
                             const bool lies = want >= 0 && want < n3[a];
-                            if ((in && (p[a] != want || !lies)) || (!wall && p[a] != want)) {
+                            if (in && (p[a] != want || !lies)) {
                                 std::printf("origin %d axis %d walls %u node %d: %d for %lld of %d\n", f, ax, walls, b,
                                             p[a], (long long)want, n3[a]);
                                 return 1;
@@ -45,7 +44,8 @@ int main() {
                         bool all = true;
                         for (int a = 0; a < 3; a++) {
                             const int64_t raw = (int64_t)org[a] + bb[a];
-                            if ((walls & (1u << a)) && (raw < 0 || raw >= n3[a])) all = false;
+                            const bool wall = walls & (1u << a);
+                            if (raw < (wall ? 0 : -n3[a]) || raw >= (wall ? n3[a] : 2 * n3[a])) all = false;
                         }
                         if (in != all) {
                             std::printf("origin %d axis %d walls %u node %d: in %d\n", f, ax, walls, b, (int)in);
