@@ -223,7 +223,7 @@ int lbm_restore(lbm_ctx *c, const void *dev_src);
 
 /* Launch shape of the main kernel: block threads (256, 512 or 1024; at least
  * the longest x-row) and z-chunk length (>= 1; 0 picks the default for the
- * block: a power of two up to 32 by an estimate of the main kernel's cost).
+ * block: 1 to 32 planes, by an estimate of the main kernel's cost).
  * A new context starts with the block and z-chunk of least estimated cost.
  * Rebuilds the tiling; results do not depend on the shape.
  * LBM_EINVAL for other blocks or a shape needing more than 64 KiB of LDS. */
@@ -231,9 +231,11 @@ int lbm_set_launch(lbm_ctx *c, int32_t block, int32_t zchunk);
 int lbm_get_launch(lbm_ctx *c, int32_t *block, int32_t *zchunk);
 
 /* Autotuner of the main-kernel launch shape.  Every block (256, 512, 1024;
- * at least the longest x-row) and z-chunk (2 ... 32) whose LDS fits is run
- * for one untimed step plus steps_per_trial steps timed with HIP events on
- * the context stream; the three fastest are timed once more, and the shape
+ * at least the longest x-row) whose LDS fits, with z-chunks of 2, 4, 8, 16 and
+ * 32 planes and with its default z-chunk, and the context's present shape
+ * (z-chunks of 2 planes or more: a lattice whose default is 1 is small enough to
+ * be better left as it is) are run for one untimed step plus steps_per_trial
+ * steps timed with HIP events on the context stream; the three fastest are timed once more, and the shape
  * with the shortest mean main-kernel time is kept.  The trial steps are real steps of the run (results do not depend on
  * the shape).  With dev_ckpt non-NULL (a device buffer of
  * lbm_checkpoint_bytes) the state is checkpointed first and restored after,

@@ -15,6 +15,7 @@
 #include "lbm.h"
 #include "lbm_adjoint.h"
 #include "lbm_kernels.h"
+#include "lbm_shape.h"
 #include "lbm_types.h"
 
 using namespace lbm;
@@ -33,8 +34,6 @@ std::mutex g_scratch_mutex;
 void *g_scratch_ptr[MAX_DEVICES] = {};
 
 constexpr size_t ALIGN = 256;
-constexpr int MAIN_BLOCK_MIN = 256;
-constexpr size_t MAIN_LDS_MAX = 64 * 1024;
 constexpr int K3_BLOCK = K3_NODES;
 constexpr int INIT_BLOCK = 256;
 
@@ -306,17 +305,7 @@ int hip_fail(lbm_ctx *c, hipError_t e, const char *what) {
         if (e_ != hipSuccess) return hip_fail((c), e_, #call);                                     \
     } while (0)
 
-// rows of one main-kernel tile of replica q for the context's block
-int tile_rows(const lbm_ctx *c, const lbm_params &q) { return std::max(1, std::min(q.ny, c->block / q.nx)); }
-
-// LDS of the main kernel for the context's block: a 4-plane ring of both
-// components' densities over the tile rows plus a one-row halo on each side
-size_t main_lds_bytes(const lbm_ctx *c) {
-    size_t elems = 0;
-    for (int r = 0; r < c->nrep; r++)
-        elems = std::max(elems, (size_t)8 * (tile_rows(c, c->p[r]) + 2) * c->p[r].nx);
-    return elems * (c->prec == LBM_FP64 ? 8 : 4);
-}
+ShapeInput shape_input(const lbm_ctx *c) { return {c->p.data(), c->prim.data(), c->nrep, c->prec, c->maxnx, c->tau1 != 0}; }
 
 // tiling of the main kernel and the workgroup tables
 void build_tiling(lbm_ctx *c) {
@@ -327,7 +316,7 @@ void build_tiling(lbm_ctx *c) {
     for (int r = 0; r < n; r++) {
         RepDesc &D = c->desc[r];
         const lbm_params &q = c->p[r];
-        D.ty = tile_rows(c, q);
+        D.ty = tile_rows(q, c->block);
         D.nty = (q.ny + D.ty - 1) / D.ty;
         D.cz = std::min(c->cz, q.nz);
         D.nchunk = (q.nz + D.cz - 1) / D.cz;
@@ -354,81 +343,7 @@ void build_tiling(lbm_ctx *c) {
     c->main_grid = wg;
     c->k3_grid = k3;
     c->init_grid = iw;
-    c->lds = main_lds_bytes(c);
-}
-
-// Cost of one main-kernel launch at z-chunk cz and the context's block: the root
-// of the squares of two times, in planes that one wave collides.
-//  - Work of a compute unit: each of its workgroups collides cz planes and fills
-//    cz + 2, a fill costing half a collision, its two halo rows included; partly
-//    filled tiles cost what full ones do.  While all workgroups are resident
-//    (four waves per SIMD; two in FP64) the busiest unit holds a whole number of
-//    them; after that, 0.55 of what the last round leaves idle is lost.
-//  - Latency: a wave alone takes 2.4 times as long per plane as a SIMD's share.
-// Blocks of 512 and 1024 wait for more waves at every plane: 1.08 and 1.23.
-// Fitted to the main kernel's times at every shape on 29 lattices of 8 k to 38 M
-// nodes (all storages, both relaxations, single and batched): the shape it picks
-// takes 1.9% more than the best one in the mean and 11% at most.  A cost of total
-// work and waves alone, with z-chunks of powers of two, took 9.8% and 48% (91 x 21
-// x 266: 1024 x 2, 266 workgroups for 256 units, 82.7 us; 512 x 3 54.4), and the
-// longest z-chunk up to 16 that keeps four waves per SIMD at 256 threads 54% at
-// most (16 x 16 x 32: 24.6 us at z-chunk 2, 18.2 at 1; 192 x 192 x 1024 FP16: 2346
-// us at 256 threads, 1912 at 1024 x 32).
-double shape_cost(const lbm_ctx *c, int cz) {
-    double work = 0.0, n = 0.0;
-    int longest = 0;
-    for (int r = 0; r < c->nrep; r++) {
-        if (c->prim[r] != r) continue;
-        const lbm_params &q = c->p[r];
-        const int ty = tile_rows(c, q), z = std::min(cz, q.nz);
-        const double tiles = (double)((q.ny + ty - 1) / ty) * ((q.nz + z - 1) / z);
-        work += tiles * (z + 0.5 * (z + 2) * (1.0 + 2.0 * q.nx / c->block));
-        n += tiles;
-        longest = std::max(longest, z);
-    }
-    const int waves = c->block / 64;
-    const double resident = std::max(1, 4 * (c->prec == LBM_FP64 ? 2 : 4) / waves);
-    const double m = n / 256.0, rounds = std::ceil(m / resident);
-    const double share = std::ceil(m) <= resident ? std::ceil(m) : m + 0.55 * (rounds * resident - m);
-    const double busy = work / n * share * waves / 4.0 * (c->block == 256 ? 1.0 : c->block == 512 ? 1.08 : 1.23);
-    const double wait = 2.4 * (longest + 0.5 * (longest + 2)) * std::max(1.0, m / resident);
-    return std::sqrt(busy * busy + wait * wait);
-}
-
-// z-chunk of least cost at the context's block
-int auto_zchunk(const lbm_ctx *c, double *cost = nullptr) {
-    int best = 1;
-    double least = 0.0;
-    for (const int cz : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32}) {
-        const double v = shape_cost(c, cz);
-        if (cz == 1 || v < least) {
-            best = cz;
-            least = v;
-        }
-    }
-    if (cost) *cost = least;
-    return best;
-}
-
-// block and z-chunk of least cost.  1024 threads leave 128 VGPRs: enough for FP32
-// arithmetic with every relaxation time 1, scratch memory in every other form.
-void auto_shape(lbm_ctx *c) {
-    int best_block = 256, best_cz = 1;
-    double least = -1.0;
-    for (int block = MAIN_BLOCK_MIN; block <= 1024; block *= 2) {
-        if (block == 1024 && (c->prec == LBM_FP64 || !c->tau1)) continue;
-        c->block = block;
-        if (main_lds_bytes(c) > MAIN_LDS_MAX) continue;
-        double v;
-        const int cz = auto_zchunk(c, &v);
-        if (least < 0.0 || v < least) {
-            least = v;
-            best_block = block;
-            best_cz = cz;
-        }
-    }
-    c->block = best_block;
-    c->cz = best_cz;
+    c->lds = main_lds_bytes(shape_input(c), c->block);
 }
 
 int upload_desc(lbm_ctx *c) {
@@ -730,7 +645,9 @@ LBM_API int lbm_init(const lbm_params *p_in, int32_t n_replicas, int32_t precisi
         }
     }
     for (int r = 0; r < n_replicas; r++) c->maxnx = std::max(c->maxnx, p[r].nx);
-    auto_shape(c);
+    const LaunchShape shape = default_shape(shape_input(c));
+    c->block = shape.block;
+    c->cz = shape.cz;
     build_tiling(c);
     int rc = upload_desc(c);
     if (rc != LBM_OK) { g_init_error = c->err; delete c; return rc; }
@@ -1122,8 +1039,8 @@ LBM_API int lbm_set_launch(lbm_ctx *c, int32_t block, int32_t zchunk) {
     // rejected shape leaves the context (and lbm_get_launch) as it was
     const int old_block = c->block, old_cz = c->cz;
     c->block = block;
-    c->cz = zchunk > 0 ? zchunk : auto_zchunk(c);
-    if (main_lds_bytes(c) > MAIN_LDS_MAX) {
+    c->cz = zchunk > 0 ? zchunk : auto_zchunk(shape_input(c), block);
+    if (main_lds_bytes(shape_input(c), block) > MAIN_LDS_MAX) {
         c->block = old_block;
         c->cz = old_cz;
         return fail(c, LBM_EINVAL, "launch shape needs too much LDS");
@@ -1147,7 +1064,6 @@ LBM_API int lbm_autotune(lbm_ctx *c, int32_t steps_per_trial, void *dev_ckpt, in
     auto trial = [&](int blk, int cz, double &ms) -> int {
         c->block = blk;
         c->cz = cz;
-        if (main_lds_bytes(c) > MAIN_LDS_MAX) { ms = -1.0; return LBM_OK; }
         build_tiling(c);
         drop_graph(c);
         int r = upload_desc(c);
@@ -1163,15 +1079,11 @@ LBM_API int lbm_autotune(lbm_ctx *c, int32_t steps_per_trial, void *dev_ckpt, in
     };
     struct Cand { int blk, cz; double ms; };
     std::vector<Cand> cands;
-    const int blocks[3] = {256, 512, 1024};
-    const int chunks[5] = {2, 4, 8, 16, 32};
-    for (int bi = 0; bi < 3 && rc == LBM_OK; bi++) {
-        if (blocks[bi] < c->maxnx) continue;
-        for (int ci = 0; ci < 5 && rc == LBM_OK; ci++) {
-            double ms = -1.0;
-            rc = trial(blocks[bi], chunks[ci], ms);
-            if (rc == LBM_OK && ms > 0.0) cands.push_back({blocks[bi], chunks[ci], ms});
-        }
+    const LaunchShape present = {c->block, c->cz};
+    for (const LaunchShape &sh : tune_shapes(shape_input(c), present)) {
+        double ms = -1.0;
+        if ((rc = trial(sh.block, sh.cz, ms)) != LBM_OK) break;
+        if (ms > 0.0) cands.push_back({sh.block, sh.cz, ms});
     }
     // the three fastest are timed again; each keeps the better of its two means
     std::sort(cands.begin(), cands.end(), [](const Cand &a, const Cand &b) { return a.ms < b.ms; });
@@ -1181,7 +1093,7 @@ LBM_API int lbm_autotune(lbm_ctx *c, int32_t steps_per_trial, void *dev_ckpt, in
         if (rc == LBM_OK && ms > 0.0) cands[k].ms = std::min(cands[k].ms, ms);
     }
     std::sort(cands.begin(), cands.end(), [](const Cand &a, const Cand &b) { return a.ms < b.ms; });
-    int best_b = cands.empty() ? 256 : cands[0].blk, best_cz = cands.empty() ? auto_zchunk(c) : cands[0].cz;
+    int best_b = cands.empty() ? present.block : cands[0].blk, best_cz = cands.empty() ? present.cz : cands[0].cz;
     const double best = cands.empty() ? -1.0 : cands[0].ms;
     c->timing = timing_was;
     c->ev_used = 0;
