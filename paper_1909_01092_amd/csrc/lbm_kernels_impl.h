@@ -1823,28 +1823,45 @@ __device__ __forceinline__ int solid_entry(int x, int y, int z, const RepDesc *d
 // position x - c_i, slot i; elements no node pulls from hold 0.  One thread per
 // padded position, consecutive ones along x.
 // Bound by HBM; the form is kept for checkpoints that outlive the process that
-// wrote them.
+// wrote them.  All of a thread's loads are issued before its first store (the two
+// buffers could be one for all the compiler knows, so that each store would
+// otherwise hold up the next load), and each XCD takes a run of neighbouring
+// blocks, whose ends share cache lines.  Save and restore, with their copies of the
+// state and the wait: 192 x 192 x 512 FP16 1111 and 1130 us before, 708 and 752 now
+// (583 for a copy of as many bytes); FP32 1375 and 1452, 1248 and 1278 (1190); 16 x
+// 16 x 32 FP32 30.4 and 27.6, 26.6 and 24.4 (24.3 and 22.4).
 template <typename S, bool SAVE>
 __global__ __launch_bounds__(256) void k_ck(CkArgs a) {
     const int r = a.rep0 + blockIdx.y;
     const RepDesc &D = a.desc[r];
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint32_t k = (uint32_t)xcd_logical(blockIdx.x, gridDim.x) * 256u + threadIdx.x;  // ck_NP has 26 bits at most
     if (D.primary != r || k >= D.ck_NP) return;
     const Geo g = geo_of(D);
-    const int px = (int)(k % (g.nx + 2)) - 1, py = (int)(k / (g.nx + 2) % (g.ny + 2)) - 1;
-    const int pz = (int)(k / ((int64_t)(g.nx + 2) * (g.ny + 2))) - 1;
+    const uint32_t row = k / (uint32_t)(g.nx + 2), plane = row / (uint32_t)(g.ny + 2);
+    const int px = (int)(k - row * (uint32_t)(g.nx + 2)) - 1, py = (int)(row - plane * (uint32_t)(g.ny + 2)) - 1;
+    const int pz = (int)plane - 1;
     S *pop = reinterpret_cast<S *>(a.pop) + D.pop_off;
     S *ck = reinterpret_cast<S *>(a.ck) + D.ck_off + k;
+    S v[2][Q];
+    uint32_t inside = 0;
 #pragma unroll
     for (int i = 0; i < Q; i++) {
         const int x = px + cx(i), y = py + cy(i), z = pz + cz(i);
         const bool in = x >= 0 && x < g.nx && y >= 0 && y < g.ny && z >= 0 && z < g.nz;
-        S *p = pop + (in ? pull_slot(x, y, z, 0, i, g) : 0);
+        inside |= in ? 1u << i : 0u;
+        const S *p = pop + (in ? pull_slot(x, y, z, 0, i, g) : 0);
+#pragma unroll
+        for (int l = 0; l < 2; l++)
+            v[l][i] = SAVE ? p[l * SLOTS.n[i] * g.nx] : ck[(int64_t)(l * Q + i) * D.ck_NP];
+    }
+#pragma unroll
+    for (int i = 0; i < Q; i++) {
+        const bool in = inside >> i & 1u;
+        S *p = pop + (in ? pull_slot(px + cx(i), py + cy(i), pz + cz(i), 0, i, g) : 0);
 #pragma unroll
         for (int l = 0; l < 2; l++) {
-            S *c = ck + (int64_t)(l * Q + i) * D.ck_NP;
-            if constexpr (SAVE) *c = in ? p[l * SLOTS.n[i] * g.nx] : S(0);
-            else if (in) p[l * SLOTS.n[i] * g.nx] = *c;
+            if constexpr (SAVE) ck[(int64_t)(l * Q + i) * D.ck_NP] = in ? v[l][i] : S(0);
+            else if (in) p[l * SLOTS.n[i] * g.nx] = v[l][i];
         }
     }
 }
