@@ -145,8 +145,9 @@ typedef struct lbm_particle {
  * (Sec. 2, force paragraph) and the settling-direction profile of v_H,z over
  * the channel cross-section, the fluid flow around the particle the set-up
  * of Sec. 3 (Fig. 1 caption) drives.  Sums run over fluid nodes in a fixed
- * order: per (x, y) column along z on the device, then the columns in order
- * on the host. */
+ * order: per (x, y) column along z on the device (in chunks of planes whose
+ * length depends on the lattice, then the chunks in order), then the columns in
+ * order on the host. */
 typedef struct lbm_obs {
     double mass[2];            /* sum of rho_l over fluid nodes                            */
     double momentum[3];        /* sum of (j_A + j_B) over fluid nodes                      */

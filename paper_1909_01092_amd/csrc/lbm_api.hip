@@ -176,8 +176,11 @@ std::string validate(const lbm_params *praw, int n, int prec, Groups &G) {
         const int nn[3] = {q.nx, q.ny, q.nz};
         if (q.nx < 2 || q.ny < 2 || q.nz < 2) return fmt("replica %d: every axis needs >= 2 nodes", r);
         if (q.nx > MAIN_BLOCK_MIN) return fmt("replica %d: nx = %d exceeds %d", r, q.nx, MAIN_BLOCK_MIN);
-        // element offsets of a replica block (38 NP) are 32-bit signed, byte
-        // offsets within one component (19 NP elements) 32-bit unsigned
+        // The kernels address a node from the base of its plane: element strides of
+        // a plane, 38 nx (ny + 2), are 32-bit signed, byte offsets from two rows
+        // before one plane to the end of the next, 38 nx (2 ny + 7) elements, 32-bit
+        // unsigned.  Both follow from the bounds on the whole below, since nz >= 2 (the
+        // offsets reach 0.993 of 2^32, on 256 x 54758 x 2 in FP32).
         const int64_t np = (int64_t)(q.nx + 2) * (q.ny + 2) * (q.nz + 2);
         const int64_t es = prec == LBM_FP64 ? 8 : prec == LBM_FP32 ? 4 : 2;
         if (np >= (int64_t(1) << 31) / 38 || 19 * np * es >= (int64_t(1) << 32))
@@ -386,8 +389,8 @@ int enqueue_step(lbm_ctx *c, bool timed, const StepScratch &sc) {
     m.tau1 = c->tau1;
     m.noise = c->noise;
     m.groups = c->groups;
-    // (rows of whole 128-byte lines gain from 300 MB on, of 64-byte halves later: the
-    // main kernel's comment has both sides)
+    // (rows of whole 128-byte lines gain from 300 MB on, of 64-byte halves from about
+    // 350: the main kernel's comment has both sides)
     const double both = 2.0 * (double)c->L.pop_elems * (double)c->es;
     m.stream = both > 350e6 ? 64 : both > 300e6 ? 128 : 0;
     if (timed && c->ev_used + 2 > c->ev.size()) {
@@ -465,7 +468,7 @@ int read_state(lbm_ctx *c, int r, RepState *s) {
 // LDS bytes (10 staged values over the tile rows plus a one-row halo on each
 // side, on the tile's plane and the planes above and below).  A workgroup
 // holds at most 160 KiB of LDS on gfx950; 1 KiB of it is left for the
-// kernel's static reduction array (416 bytes).
+// kernel's static reduction array (128 bytes).
 constexpr size_t ADJ_LDS_MAX = 160 * 1024 - 1024;
 int adj_tile_rows(const lbm_params &q) { return std::max(1, std::min(q.ny, 256 / q.nx)); }
 size_t adj_lds_bytes(const lbm_params &q, int prec) {

@@ -445,7 +445,8 @@ __device__ __forceinline__ int xcd_logical(int b, int G) {
 // computation lives in the bounding-box kernels.
 // FP32 arithmetic with all relaxation times 1 (FP32 or FP16 storage): both
 // components unrolled and the kernel held to 128 VGPRs (four waves per SIMD).
-// Other forms keep the component loop rolled and their natural allocation.
+// Other forms keep the component loop rolled and at least three waves per SIMD
+// (FP32) or two (FP64).
 template <typename S, typename T, bool TAU1>
 constexpr bool main_fast_form = sizeof(T) == 4 && TAU1;
 template <typename S, typename T, bool TAU1>
@@ -485,12 +486,20 @@ void k_main(MainArgs a) {
     // before memory (both buffers over 300 MB where a row's slots fill whole 128-byte
     // lines, over 350 MB where they fill 64-byte halves); FP32 and FP64.  Plain and
     // non-temporal, us: 192 ensemble channels (9.9 GB) 2437 and 2265, 64 x 64 x 256
-    // (319 MB) 86.6 and 83.1, 128^3 160 and 152, 64 x 64 x 200 FP64 211 and 194;
-    // halves: 9 x 48^3 (328 MB) 85.2 and 88.1, 3 x 48 x 48 x 192 (430 MB) 124.4 and
-    // 120.6.  Smaller ones lose the cache (64 x 64 x 224, 279 MB: 77.2 and 78.9; 6 x
-    // 32 x 32 x 128, 239 MB: 63.7 and 69.4), rows of other lengths write lines in
-    // parts (60 x 60 x 900: 290 and 326), and FP16 gains nothing (192 x 192 x 1024:
-    // 1937 and 1917; 96 x 96 x 512: 323 and 328).
+    // (319 MB) 86.6 and 83.1, 128^3 160 and 152, 64 x 64 x 200 FP64 211 and 194.
+    // Gain of a step, in one and in nine replicas of rows of nx nodes, by the size of
+    // both buffers (MB):
+    //              260          300          325          350          430          700
+    //   FP32 64    0.91 0.91    0.99 0.98    1.02 1.02    1.07 1.05    1.02 1.02    1.05 1.05
+    //        32    0.87 0.85    1.00 0.98    1.04 1.03    1.07 1.06    1.02 1.03    1.05 1.05
+    //   (halves)
+    //        48    0.85 0.85    0.97 0.94    1.01 1.00    1.03 1.00    1.03 1.03    1.05 1.05
+    //        16    0.79 0.78    0.95 0.93    0.98 0.98    1.02 1.01    1.01 1.01    1.04 1.04
+    //        80    0.87 0.86    0.95 0.91    1.00 0.92    1.03 1.00    1.01 1.01    1.04 1.04
+    //       112    0.84 0.85    0.97 0.91    0.99 0.94    0.99 0.95    1.02 1.04    1.04 1.05
+    //   FP64 40    0.98 1.00    1.02 1.00    1.04 1.03    1.04 1.04    1.06 1.04    1.04 1.04
+    // Rows of other lengths write lines in parts (60 x 60 x 900: 290 and 326 us), and
+    // FP16 gains nothing (192 x 192 x 1024: 1937 and 1917; 96 x 96 x 512: 323 and 328).
     const bool stream = sizeof(S) >= 4 && a.stream && ((nx * (int)sizeof(S)) & (a.stream - 1)) == 0;
     const bool hp = D.has_particle;
     const int nsph = GROUP ? D.n_sph : 1;

@@ -43,8 +43,10 @@ inline size_t main_lds_bytes(const ShapeInput &in, int block) {
 //  - Work of a compute unit: each of its workgroups collides cz planes and fills
 //    cz + 2, a fill costing half a collision, its two halo rows included; partly
 //    filled tiles cost what full ones do.  While all workgroups are resident
-//    (four waves per SIMD; two in FP64) the busiest unit holds a whole number of
-//    them; after that, 0.55 of what the last round leaves idle is lost.
+//    the busiest unit holds a whole number of them; after that, 0.55 of what the
+//    last round leaves idle is lost.  Resident are taken to be four waves per SIMD,
+//    two in FP64, as the fit was made; by their registers FP64 with every relaxation
+//    time 1 (140 and 165) and FP16 general relaxation with noise (136) run at three.
 //  - Latency: a wave alone takes 2.4 times as long per plane as a SIMD's share.
 // Blocks of 512 and 1024 wait for more waves at every plane: 1.08 and 1.23.
 // Fitted to the main kernel's times at every shape on 29 lattices of 8 k to 38 M
@@ -91,8 +93,13 @@ inline int auto_zchunk(const ShapeInput &in, int block, double *cost = nullptr) 
     return best;
 }
 
-// block and z-chunk of least cost.  1024 threads leave 128 VGPRs: enough for FP32
-// arithmetic with every relaxation time 1, scratch memory in every other form.
+// block and z-chunk of least cost.  1024 threads, which leave 128 VGPRs, are taken
+// with FP32 arithmetic and every relaxation time 1 only.  FP64 spills 12 to 141
+// registers there.  General relaxation fits in FP32 (no spill) and gains nothing:
+// best at 512 and at 1024 threads 107.3 and 106.7 us on 64 x 64 x 256, 152.6 and
+// 157.8 on 150 x 64 x 128, 814 and 832 on 192 x 192 x 256.  In FP16 it spills two or
+// three with noise, none without, and is faster on most lattices (102 and 92, 146
+// and 127, 1017 and 732), which tuning finds; the cost above was not fitted to it.
 inline LaunchShape default_shape(const ShapeInput &in) {
     LaunchShape best = {MAIN_BLOCK_MIN, 1};
     double least = -1.0;
